@@ -469,7 +469,7 @@ def _evaluate(p, system, T, with_forces):
             else:
                 e = network(x, en, dims + [1], 0)[:, 0]
         energy = e.sum()
-    out = dict(energy=float(energy.detach()), atoms=e.detach().cpu().numpy())
+    out = dict(energy=np.float64(energy.detach().item()), atoms=e.detach().cpu().numpy())
     if with_forces:
         g = torch.autograd.grad(energy, [d for _, _, d, _ in edges])
         F, W = torch.zeros_like(pos), torch.zeros(3, 3, dtype=torch.float64, device=dev)
