@@ -113,6 +113,28 @@ struct PinnedWord {
     double *get_double() { return reinterpret_cast<double *>(get()); }   // the 64 bytes as doubles
 };
 
+// Pinned host memory that kernels write directly (read after a wait for the stream).
+struct PinnedWords {
+    int64_t *p = nullptr;
+    size_t bytes = 0;
+    PinnedWords() = default;
+    PinnedWords(const PinnedWords &) = delete;
+    PinnedWords &operator=(const PinnedWords &) = delete;
+    ~PinnedWords() {
+        if (p) (void)hipHostFree(p);
+    }
+    int64_t *get(size_t n) {
+        if (n > bytes) {
+            if (p) (void)hipHostFree(p);
+            p = nullptr;
+            bytes = 0;
+            HIP_OK(hipHostMalloc((void **)&p, n, hipHostMallocDefault));
+            bytes = n;
+        }
+        return p;
+    }
+};
+
 template <class T> struct DArr {
     DevBuf b;
     size_t n = 0;

@@ -659,13 +659,14 @@ __global__ void k_gather(int64_t n, int64_t n_gh, int K, const int32_t *__restri
 }
 
 template <typename R>
-__global__ void k_reduce(int64_t n, int width, const int32_t *__restrict__ ptr, const int32_t *__restrict__ idx,
+__global__ void k_reduce(int64_t n, int width, const int2 *__restrict__ rng, const int32_t *__restrict__ idx,
                          R *__restrict__ v) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n * width) return;
     const int64_t o = t / width, m = t % width;
     R s = v[o * width + m];
-    for (int32_t q = ptr[o]; q < ptr[o + 1]; ++q) s += v[(n + idx[q]) * width + m];
+    const int2 c = rng[o];
+    for (int q = c.x; q < c.y; ++q) s += v[(n + idx[q]) * width + m];
     v[o * width + m] = s;
 }
 
@@ -686,11 +687,11 @@ void ghost_gather(hipStream_t st, bool fp64, int64_t n, int64_t n_gh, int K, con
     LAUNCH_OK("k_gather");
 }
 
-void ghost_reduce(hipStream_t st, bool fp64, int64_t n, int width, const int32_t *copy_ptr, const int32_t *copy_idx,
+void ghost_reduce(hipStream_t st, bool fp64, int64_t n, int width, const int2 *copy_rng, const int32_t *copy_idx,
                   void *v) {
     const int64_t tot = n * width;
-    if (fp64) hipLaunchKernelGGL(k_reduce<double>, dim3(grid_for(tot, 256)), dim3(256), 0, st, n, width, copy_ptr, copy_idx, (double *)v);
-    else hipLaunchKernelGGL(k_reduce<float>, dim3(grid_for(tot, 256)), dim3(256), 0, st, n, width, copy_ptr, copy_idx, (float *)v);
+    if (fp64) hipLaunchKernelGGL(k_reduce<double>, dim3(grid_for(tot, 256)), dim3(256), 0, st, n, width, copy_rng, copy_idx, (double *)v);
+    else hipLaunchKernelGGL(k_reduce<float>, dim3(grid_for(tot, 256)), dim3(256), 0, st, n, width, copy_rng, copy_idx, (float *)v);
     LAUNCH_OK("k_reduce");
 }
 

@@ -63,8 +63,8 @@ int edge_backward_blocks(int64_t n_ext);
 
 // c[n + g][:] = c[owner[g]][:]
 void ghost_gather(hipStream_t st, bool fp64, int64_t n, int64_t n_gh, int K, const int32_t *owner, void *c);
-// v[o][:] += sum over ghost copies g of o of v[n + g][:], in increasing g
-void ghost_reduce(hipStream_t st, bool fp64, int64_t n, int width, const int32_t *copy_ptr, const int32_t *copy_idx,
+// v[o][:] += sum over ghost copies g of o of v[n + g][:], in copy-list order
+void ghost_reduce(hipStream_t st, bool fp64, int64_t n, int width, const int2 *copy_rng, const int32_t *copy_idx,
                   void *v);
 // c^0 of every ext atom from its species
 void init_messages(hipStream_t st, bool fp64, int64_t n_ext, int K, const int8_t *spec, const void *c0, void *c);

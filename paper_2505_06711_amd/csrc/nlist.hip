@@ -95,59 +95,63 @@ __global__ void k_wrap_count(Geom g, int64_t n, const double *__restrict__ pos, 
             if (ww >= g.lo[a][k] && ww < g.hi[a][k]) c[a] = k;
     }
     dom[u] = (c[0] * g.P[1] + c[1]) * g.P[2] + c[2];
-    int64_t cnt = 0;
-    for (int s0 = -g.nm[0]; s0 <= g.nm[0]; ++s0)
-        for (int s1 = -g.nm[1]; s1 <= g.nm[1]; ++s1)
-            for (int s2 = -g.nm[2]; s2 <= g.nm[2]; ++s2) {
-                int s[3] = {s0, s1, s2};
-                unsigned m[3];
-                for (int a = 0; a < 3; ++a) {
-                    double y = g.per[a] ? wu[a] + (double)s[a] * g.L[a] : wu[a];
-                    m[a] = axis_domains(g, a, y);
-                }
-                int k = __popc(m[0]) * __popc(m[1]) * __popc(m[2]);
-                if (s0 == 0 && s1 == 0 && s2 == 0) k -= 1;   // the atom itself in its own subdomain
-                cnt += k;
-            }
-    gcount[u] = cnt;
+    // copies = (shift, subdomain) combinations whose shell holds the shifted atom, less the atom
+    // itself in its own subdomain; the axes are independent, so the count is a product
+    int64_t cnt = 1;
+    for (int a = 0; a < 3; ++a) {
+        int k = 0;
+        for (int s = -g.nm[a]; s <= g.nm[a]; ++s)
+            k += __popc(axis_domains(g, a, g.per[a] ? wu[a] + (double)s * g.L[a] : wu[a]));
+        cnt *= k;
+    }
+    gcount[u] = cnt - 1;
 }
 
+// The copies of every atom in the order (shift, subdomain), from goff[u]; each axis' shift is
+// tested before the axes inside it, so an atom far from every boundary tests few of them.  The
+// same launch clears the key counts (count[0 .. ncount)).
 __global__ void k_ghost_gen(Geom g, int64_t n, const double *__restrict__ w, const int32_t *__restrict__ dom,
                             const int64_t *__restrict__ goff, int32_t *__restrict__ g_owner, int32_t *__restrict__ g_shift,
-                            int32_t *__restrict__ g_dom, double *__restrict__ g_pos) {
+                            int32_t *__restrict__ g_dom, double *__restrict__ g_pos, int32_t *__restrict__ count,
+                            int64_t ncount) {
     int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u < ncount) count[u] = 0;
     if (u >= n) return;
     int64_t o = goff[u];
     if (goff[u + 1] == o) return;   // no copies (also the case of a flagged atom)
-    double wu[3] = {w[3 * u], w[3 * u + 1], w[3 * u + 2]};
-    int own = dom[u];
-    for (int s0 = -g.nm[0]; s0 <= g.nm[0]; ++s0)
-        for (int s1 = -g.nm[1]; s1 <= g.nm[1]; ++s1)
+    const double wu[3] = {w[3 * u], w[3 * u + 1], w[3 * u + 2]};
+    const int own = dom[u];
+    auto at = [&](int a, int s) { return g.per[a] ? wu[a] + (double)s * g.L[a] : wu[a]; };
+    for (int s0 = -g.nm[0]; s0 <= g.nm[0]; ++s0) {
+        const double y0 = at(0, s0);
+        const unsigned m0 = axis_domains(g, 0, y0);
+        if (!m0) continue;
+        for (int s1 = -g.nm[1]; s1 <= g.nm[1]; ++s1) {
+            const double y1 = at(1, s1);
+            const unsigned m1 = axis_domains(g, 1, y1);
+            if (!m1) continue;
             for (int s2 = -g.nm[2]; s2 <= g.nm[2]; ++s2) {
-                int s[3] = {s0, s1, s2};
-                unsigned m[3];
-                double y[3];
-                for (int a = 0; a < 3; ++a) {
-                    y[a] = g.per[a] ? wu[a] + (double)s[a] * g.L[a] : wu[a];
-                    m[a] = axis_domains(g, a, y[a]);
-                }
+                const double y2 = at(2, s2);
+                const unsigned m2 = axis_domains(g, 2, y2);
                 for (int k0 = 0; k0 < g.P[0]; ++k0) {
-                    if (!(m[0] >> k0 & 1u)) continue;
+                    if (!(m0 >> k0 & 1u)) continue;
                     for (int k1 = 0; k1 < g.P[1]; ++k1) {
-                        if (!(m[1] >> k1 & 1u)) continue;
+                        if (!(m1 >> k1 & 1u)) continue;
                         for (int k2 = 0; k2 < g.P[2]; ++k2) {
-                            if (!(m[2] >> k2 & 1u)) continue;
+                            if (!(m2 >> k2 & 1u)) continue;
                             int p = (k0 * g.P[1] + k1) * g.P[2] + k2;
                             if (s0 == 0 && s1 == 0 && s2 == 0 && p == own) continue;
                             g_owner[o] = (int32_t)u;
                             g_shift[3 * o] = s0; g_shift[3 * o + 1] = s1; g_shift[3 * o + 2] = s2;
                             g_dom[o] = p;
-                            g_pos[3 * o] = y[0]; g_pos[3 * o + 1] = y[1]; g_pos[3 * o + 2] = y[2];
+                            g_pos[3 * o] = y0; g_pos[3 * o + 1] = y1; g_pos[3 * o + 2] = y2;
                             ++o;
                         }
                     }
                 }
             }
+        }
+    }
 }
 
 struct Bins {
@@ -186,11 +190,6 @@ __global__ void k_keys(Bins b, int ndom, int n_species, int64_t n, int64_t n_gh,
     int64_t k = ((int64_t)slot * ndom + p) * b.nbin + bn;
     key[e] = k;
     atomicAdd(&count[k], 1);
-}
-
-__global__ void k_i32_to_i64(const int32_t *__restrict__ a, int64_t *__restrict__ b, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = a[i];
 }
 
 __global__ void k_scatter(int64_t m, const int64_t *__restrict__ key, const int64_t *__restrict__ kstart,
@@ -236,22 +235,10 @@ __global__ __launch_bounds__(256) void k_sort_segments(int64_t nseg, const int64
     }
 }
 
-__global__ void k_sort_segments32(int64_t nseg, const int32_t *__restrict__ start, int32_t *__restrict__ v) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nseg) return;
-    int32_t a = start[k], e = start[k + 1];
-    for (int32_t i = a + 1; i < e; ++i) {
-        int32_t x = v[i];
-        int32_t j = i - 1;
-        while (j >= a && v[j] > x) { v[j + 1] = v[j]; --j; }
-        v[j + 1] = x;
-    }
-}
-
 // rev[f] for the entry f = (x -> j) of a sorted list: the slot of (j -> x) in row j.  Every
 // entry has one: rows of locals list every ext atom in range, rows of ghosts every local in
 // range, and a row of a ghost only holds locals.  Each pair is resolved once, from its entry
-// with x < j (a binary search for x in row j), which writes both slots; rev starts at -1, and
+// with x < j (a binary search for x in row j), which writes both slots; rev starts at -1 (k_rows), and
 // k_reverse_check then sets *bad if a slot was not written (an entry without its reverse).
 __global__ void k_reverse(int64_t n_ext, const int64_t *__restrict__ row, const int32_t *__restrict__ col,
                           int32_t *__restrict__ rev, int32_t *__restrict__ bad) {
@@ -284,13 +271,18 @@ __global__ void k_reverse_check(int64_t n_pairs, const int32_t *__restrict__ rev
     if (f < n_pairs && rev[f] < 0) atomicOr(bad, 1);
 }
 
+// The ext atoms in key order.  An owner's ghost copies were generated one after another (goff),
+// so its copy list is that range, with each copy's final ghost index at its place.
 __global__ void k_build_ext(Bins b, int64_t n, int64_t n_ext, const int32_t *__restrict__ order,
-                            const double *__restrict__ w, const int32_t *__restrict__ dom, const int32_t *__restrict__ species,
-                            const double *__restrict__ g_pos, const int32_t *__restrict__ g_dom,
-                            const int32_t *__restrict__ g_owner_user, const int32_t *__restrict__ g_shift_in,
-                            int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm, double *__restrict__ pext,
-                            int32_t *__restrict__ dom_ext, int32_t *__restrict__ bin_ext, int8_t *__restrict__ spec_ext,
-                            int32_t *__restrict__ gh_owner_user, int32_t *__restrict__ gh_shift) {
+                            const double *__restrict__ pos, const double *__restrict__ w,
+                            const int32_t *__restrict__ dom, const int32_t *__restrict__ species,
+                            const int64_t *__restrict__ goff, const double *__restrict__ g_pos,
+                            const int32_t *__restrict__ g_dom, const int32_t *__restrict__ g_owner_user,
+                            const int32_t *__restrict__ g_shift_in, int32_t *__restrict__ perm,
+                            int32_t *__restrict__ inv_perm, double *__restrict__ pext, int32_t *__restrict__ dom_ext,
+                            int32_t *__restrict__ bin_ext, int8_t *__restrict__ spec_ext,
+                            int32_t *__restrict__ gh_owner_user, int32_t *__restrict__ gh_shift,
+                            int2 *__restrict__ copy_rng, int32_t *__restrict__ copy_idx, double *__restrict__ xref) {
     int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= n_ext) return;
     int64_t pre = order[x];
@@ -301,12 +293,15 @@ __global__ void k_build_ext(Bins b, int64_t n, int64_t n_ext, const int32_t *__r
         y = w + 3 * pre;
         dom_ext[x] = dom[pre];
         spec_ext[x] = (int8_t)species[pre];
+        copy_rng[x] = make_int2((int)goff[pre], (int)goff[pre + 1]);
+        for (int a = 0; a < 3; ++a) xref[3 * x + a] = pos[3 * pre + a];
     } else {
         int64_t gi = pre - n, go = x - n;
         y = g_pos + 3 * gi;
         dom_ext[x] = g_dom[gi];
         int32_t ou = g_owner_user[gi];
         gh_owner_user[go] = ou;
+        copy_idx[gi] = (int32_t)go;
         spec_ext[x] = (int8_t)species[ou];
         for (int a = 0; a < 3; ++a) gh_shift[3 * go + a] = g_shift_in[3 * gi + a];
     }
@@ -316,188 +311,145 @@ __global__ void k_build_ext(Bins b, int64_t n, int64_t n_ext, const int32_t *__r
     bin_ext[x] = bin_of(b, y);
 }
 
-__global__ void k_ghost_owner(int64_t n_gh, const int32_t *__restrict__ owner_user, const int32_t *__restrict__ inv_perm,
-                              int32_t *__restrict__ owner) {
-    int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < n_gh) owner[g] = inv_perm[owner_user[g]];
-}
-
 // Candidate scan over the 27 bins around atom x of its subdomain.  Locals see every ext atom
-// of the subdomain; ghosts see only locals.  A half-wave (32 lanes) takes a row: the keys in
-// increasing order (slot, then the stencil's bins by index), and each key's atoms 32 at a
-// time, one per lane, so that the atoms' positions are read contiguously.  Ext atoms are
-// numbered in key order, so the row comes out with its columns ascending.  The count pass
-// keeps each 32-atom chunk's hits as one word (up to cap_words chunks per row) and the fill
-// replays them; a row with more chunks is measured again by the fill.
+// of the subdomain; ghosts see only locals.  Keys number a bin column's bins consecutively, so
+// the three bins of a stencil column hold one run of ext atoms: a row's candidates are 9 runs
+// per slot.  A half-wave (32 lanes) takes a row; for up to 3 slots at a time (27 runs) its
+// lanes read the runs' bounds together, sum their lengths, and then walk the runs end to end,
+// 32 candidates a word, so that short runs (small bins, several elements) leave no lanes idle
+// and a lane's position loads do not wait for one another.  Runs are in key order and ext atoms
+// are numbered in key order, so the row comes out with its columns ascending.  The count pass
+// keeps each word's hits (up to cap_words words a row) and the fill replays them; a row with
+// more words is measured again by the fill.
+//
+// Bound by load latency (few rows) and FP64 issue (many).  Before, rows whose keys held under 24
+// atoms on average took a thread each and the others a half-wave that walked its runs one bin at
+// a time.  Count + fill, before -> now: 3,000-atom water box (8,600 rows) 266 + 181 -> 14 + 19 us;
+// 100,800-atom crystal 318 + 177 -> 183 + 144 us; 1.2M-atom water split 2x2x2 (1.68M rows)
+// 1,724 + 1,525 -> 1,730 + 1,825 us, the fill now also clearing the reverse slots (a 0.42 GB
+// memset before).
 constexpr int kRowsPerBlk = 8;   // 256 threads, a half-wave per row
+constexpr int kRunSlots = 3;     // slots whose runs (9 each) are walked together
+constexpr int kRowUnroll = 4;    // words whose positions are loaded together
 
 template <bool FILL>
-__global__ __launch_bounds__(256) void k_rows_group(Bins b, Geom g, int n_species, int n_ghost_slots, int64_t n, int64_t n_ext,
+__global__ __launch_bounds__(256) void k_rows(Bins b, Geom g, int n_species, int n_ghost_slots, int64_t n, int64_t n_ext,
                                               const double *__restrict__ pext, const int32_t *__restrict__ dom_ext,
                                               const int32_t *__restrict__ bin_ext, const int64_t *__restrict__ kstart,
                                               int64_t *__restrict__ rowcnt, const int64_t *__restrict__ row,
-                                              int32_t *__restrict__ col, int32_t *__restrict__ coincident,
-                                              uint32_t *__restrict__ mask, int32_t *__restrict__ nchunk, int cap_words) {
-    const int64_t x = (int64_t)blockIdx.x * kRowsPerBlk + (threadIdx.x >> 5);
+                                              int32_t *__restrict__ col, int32_t *__restrict__ rev,
+                                              int32_t *__restrict__ coincident, uint32_t *__restrict__ mask,
+                                              int32_t *__restrict__ nwords, int cap_words,
+                                              const int32_t *__restrict__ gh_owner_user,
+                                              const int32_t *__restrict__ inv_perm, int32_t *__restrict__ gh_owner) {
+    __shared__ int32_t s_off[kRowsPerBlk][33], s_beg[kRowsPerBlk][32];
+    const int hw = threadIdx.x >> 5;
+    const int64_t x = (int64_t)blockIdx.x * kRowsPerBlk + hw;
     const int lane = threadIdx.x & 31, half = threadIdx.x & 32;
     if (x >= n_ext) return;   // the whole half-wave
+    // a ghost's owner in local numbering (every inv_perm entry is in place by now)
+    if (!FILL && lane == 0 && x >= n) gh_owner[x - n] = inv_perm[gh_owner_user[x - n]];
     const double xi = pext[x], yi = pext[n_ext + x], zi = pext[2 * n_ext + x];
     const int p = dom_ext[x];
     const int bx = bin_ext[x];
     const int c2 = bx % b.nb[2], c1 = (bx / b.nb[2]) % b.nb[1], c0 = bx / (b.nb[2] * b.nb[1]);
+    const int lo2 = max(c2 - 1, 0), hi2 = min(c2 + 1, b.nb[2] - 1);
     const int nslot = (x < n) ? n_species + n_ghost_slots : n_species;
     uint32_t *mrow = mask + x * cap_words;
-    const int nkept = FILL ? nchunk[x] : 0;
+    const int nkept = FILL ? nwords[x] : 0;
     const bool replay = FILL && nkept <= cap_words;
-    int64_t cnt = 0, o = FILL ? row[x] : 0;
-    int q = 0;   // chunks so far
+    int64_t o = FILL ? row[x] : 0;
+    int cnt = 0;
+    int q = 0;   // words so far
     // replay: the row's words are read 32 at a time, one per lane, and passed round by shuffles
     uint32_t wbuf = 0;
     int wbase = -32;
-    for (int slot = 0; slot < nslot; ++slot) {
-        for (int d0 = -1; d0 <= 1; ++d0) {
-            const int a0 = c0 + d0;
-            if (a0 < 0 || a0 >= b.nb[0]) continue;
-            for (int d1 = -1; d1 <= 1; ++d1) {
-                const int a1 = c1 + d1;
-                if (a1 < 0 || a1 >= b.nb[1]) continue;
-                for (int d2 = -1; d2 <= 1; ++d2) {
-                    const int a2 = c2 + d2;
-                    if (a2 < 0 || a2 >= b.nb[2]) continue;
-                    const int64_t bn = ((int64_t)a0 * b.nb[1] + a1) * b.nb[2] + a2;
-                    const int64_t k = ((int64_t)slot * g.ndom + p) * b.nbin + bn;
-                    const int64_t s0 = kstart[k], s1 = kstart[k + 1];
-                    for (int64_t t0 = s0; t0 < s1; t0 += 32, ++q) {
-                        const int64_t e = t0 + lane;
-                        uint32_t bits;
-                        if (replay) {
-                            if (q >= wbase + 32) {
-                                wbase = q;
-                                wbuf = q + lane < nkept ? mrow[q + lane] : 0u;
-                            }
-                            bits = (uint32_t)__shfl((int)wbuf, q - wbase, 32);
-                        } else {
-                            bool hit = false;
-                            if (e < s1 && e != x) {
-                                const double dx = pext[e] - xi, dy = pext[n_ext + e] - yi, dz = pext[2 * n_ext + e] - zi;
-                                const double dd = fma(dz, dz, fma(dy, dy, dx * dx));
-                                hit = dd < g.rc2;
-                                // two copies closer than 1e-6 A: the pair direction is undefined
-                                if (!FILL && dd < 1e-12) atomicOr(coincident, 1);
-                            }
-                            bits = (uint32_t)(__ballot(hit) >> half);
-                        }
-                        if (FILL) {
-                            if ((bits >> lane) & 1u) col[o + __popc(bits & ((1u << lane) - 1u))] = (int32_t)e;
-                            o += __popc(bits);
-                        } else {
-                            cnt += __popc(bits);
-                            if (lane == 0 && q < cap_words) mrow[q] = bits;
-                        }
-                    }
+    int32_t *off = s_off[hw], *beg = s_beg[hw];
+    for (int s0 = 0; s0 < nslot; s0 += kRunSlots) {
+        // lane r: run r of the batch (slot s0 + r / 9, column r % 9), its first atom and length
+        const int sl = s0 + lane / 9, dd = lane % 9;
+        const int a0 = c0 + dd / 3 - 1, a1 = c1 + dd % 3 - 1;
+        int first = 0, len = 0;
+        if (lane < 9 * kRunSlots && sl < nslot && a0 >= 0 && a0 < b.nb[0] && a1 >= 0 && a1 < b.nb[1]) {
+            const int64_t k = ((int64_t)sl * g.ndom + p) * b.nbin + ((int64_t)a0 * b.nb[1] + a1) * b.nb[2];
+            first = (int)kstart[k + lo2];
+            len = (int)(kstart[k + hi2 + 1] - first);
+        }
+        int end = len;
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) {
+            const int t = __shfl_up(end, d, 32);
+            if (lane >= d) end += t;
+        }
+        const int total = __shfl(end, 31, 32);
+        // the half-wave's own table (LDS accesses of a wave complete in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        off[lane + 1] = end;
+        if (lane == 0) off[0] = 0;
+        beg[lane] = first;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        int r = 0;   // run of this lane's candidate
+        auto atom = [&](int c) -> int {   // c < total, not below the last one asked for
+            while (c >= off[r + 1]) ++r;
+            return beg[r] + (c - off[r]);
+        };
+        if (replay) {
+            for (int w0 = 0; w0 < total; w0 += 32, ++q) {
+                if (q >= wbase + 32) {
+                    wbase = q;
+                    wbuf = q + lane < nkept ? mrow[q + lane] : 0u;
                 }
+                const uint32_t bits = (uint32_t)__shfl((int)wbuf, q - wbase, 32);
+                if ((bits >> lane) & 1u) {
+                    const int64_t d = o + __popc(bits & ((1u << lane) - 1u));
+                    col[d] = atom(w0 + lane);
+                    rev[d] = -1;   // not resolved yet
+                }
+                o += __popc(bits);
+            }
+            continue;
+        }
+        for (int w0 = 0; w0 < total; w0 += 32 * kRowUnroll) {
+            int e[kRowUnroll];
+            double ex[kRowUnroll], ey[kRowUnroll], ez[kRowUnroll];
+#pragma unroll
+            for (int u = 0; u < kRowUnroll; ++u) {
+                const int c = w0 + 32 * u + lane;
+                e[u] = c < total ? atom(c) : (int)x;   // past the end: the atom itself, never a hit
+            }
+#pragma unroll
+            for (int u = 0; u < kRowUnroll; ++u) {
+                ex[u] = pext[e[u]]; ey[u] = pext[n_ext + e[u]]; ez[u] = pext[2 * n_ext + e[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < kRowUnroll; ++u) {
+                if (w0 + 32 * u >= total) break;   // uniform over the half-wave
+                const double dx = ex[u] - xi, dy = ey[u] - yi, dz = ez[u] - zi;
+                const double dd2 = fma(dz, dz, fma(dy, dy, dx * dx));
+                const bool hit = e[u] != (int)x && dd2 < g.rc2;
+                // two copies closer than 1e-6 A: the pair direction is undefined
+                if (!FILL && e[u] != (int)x && dd2 < 1e-12) atomicOr(coincident, 1);
+                const uint32_t bits = (uint32_t)(__ballot(hit) >> half);
+                if (FILL) {
+                    if (hit) {
+                        const int64_t d = o + __popc(bits & ((1u << lane) - 1u));
+                        col[d] = e[u];
+                        rev[d] = -1;
+                    }
+                    o += __popc(bits);
+                } else {
+                    cnt += __popc(bits);
+                    if (lane == 0 && q < cap_words) mrow[q] = bits;
+                }
+                ++q;
             }
         }
     }
     if (!FILL && lane == 0) {
         rowcnt[x] = cnt;
-        nchunk[x] = q;
+        nwords[x] = q;
     }
-}
-
-// The candidate scan (see k_rows_group) with a thread per row, each taking its candidates one
-// by one: the count pass keeps the hits as bits over the row's candidates (up to 32 cap_words),
-// and the fill replays them.  Suits rows whose keys hold few atoms (several elements, small
-// bins), where most lanes of a group would idle.
-template <bool FILL>
-__global__ void k_rows_thread(Bins b, Geom g, int n_species, int n_ghost_slots, int64_t n, int64_t n_ext, const double *__restrict__ pext,
-                       const int32_t *__restrict__ dom_ext, const int32_t *__restrict__ bin_ext,
-                       const int64_t *__restrict__ kstart, int64_t *__restrict__ rowcnt, const int64_t *__restrict__ row,
-                       int32_t *__restrict__ col, int32_t *__restrict__ coincident, uint32_t *__restrict__ mask,
-                       int32_t *__restrict__ ncand, int cap_words) {
-    int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= n_ext) return;
-    const double xi = pext[x], yi = pext[n_ext + x], zi = pext[2 * n_ext + x];
-    const int p = dom_ext[x];
-    const int bx = bin_ext[x];
-    const int c2 = bx % b.nb[2], c1 = (bx / b.nb[2]) % b.nb[1], c0 = bx / (b.nb[2] * b.nb[1]);
-    const int nslot = (x < n) ? n_species + n_ghost_slots : n_species;
-    const int64_t cap_bits = (int64_t)cap_words * 32;
-    uint32_t *mrow = mask + x * cap_words;
-    // the fill replays the count pass's hits from its bits when they fitted, else it measures
-    // the distances again
-    const bool replay = FILL && ncand[x] <= cap_bits;
-    int64_t cnt = 0, o = FILL ? row[x] : 0, ci = 0;
-    uint32_t word = 0;
-    // keys in increasing order (slot, then the stencil's bins by index): ext atoms are numbered
-    // in key order, so a row comes out with its columns ascending; ci numbers the candidates in
-    // this order
-    for (int slot = 0; slot < nslot; ++slot) {
-        for (int d0 = -1; d0 <= 1; ++d0) {
-            int a0 = c0 + d0;
-            if (a0 < 0 || a0 >= b.nb[0]) continue;
-            for (int d1 = -1; d1 <= 1; ++d1) {
-                int a1 = c1 + d1;
-                if (a1 < 0 || a1 >= b.nb[1]) continue;
-                for (int d2 = -1; d2 <= 1; ++d2) {
-                    int a2 = c2 + d2;
-                    if (a2 < 0 || a2 >= b.nb[2]) continue;
-                    int64_t bn = ((int64_t)a0 * b.nb[1] + a1) * b.nb[2] + a2;
-                    int64_t k = ((int64_t)slot * g.ndom + p) * b.nbin + bn;
-                    for (int64_t e = kstart[k]; e < kstart[k + 1]; ++e, ++ci) {
-                        if (replay) {
-                            if ((ci & 31) == 0) word = mrow[ci >> 5];
-                            if ((word >> (ci & 31)) & 1u) col[o++] = (int32_t)e;
-                            continue;
-                        }
-                        bool hit = false;
-                        if (e != x) {
-                            double dx = pext[e] - xi, dy = pext[n_ext + e] - yi, dz = pext[2 * n_ext + e] - zi;
-                            double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
-                            hit = d2 < g.rc2;
-                            // two copies closer than 1e-6 A: the pair direction is undefined
-                            if (!FILL && d2 < 1e-12) atomicOr(coincident, 1);
-                        }
-                        if (FILL) {
-                            if (hit) col[o++] = (int32_t)e;
-                        } else {
-                            if (hit) {
-                                ++cnt;
-                                word |= 1u << (ci & 31);
-                            }
-                            if ((ci & 31) == 31) {
-                                if ((ci >> 5) < cap_words) mrow[ci >> 5] = word;
-                                word = 0;
-                            }
-                        }
-                    }
-                }
-            }
-        }
-    }
-    if (!FILL) {
-        if ((ci & 31) != 0 && (ci >> 5) < cap_words) mrow[ci >> 5] = word;   // the last, partial word
-        rowcnt[x] = cnt;
-        ncand[x] = ci < INT32_MAX ? (int32_t)ci : INT32_MAX;
-    }
-}
-
-__global__ void k_copy_count(int64_t n_gh, const int32_t *__restrict__ owner, int32_t *__restrict__ cnt) {
-    int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gi < n_gh) atomicAdd(&cnt[owner[gi]], 1);
-}
-
-__global__ void k_copy_fill(int64_t n_gh, const int32_t *__restrict__ owner, const int64_t *__restrict__ start,
-                            int32_t *__restrict__ cursor, int32_t *__restrict__ idx) {
-    int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gi >= n_gh) return;
-    int32_t o = owner[gi];
-    idx[start[o] + atomicAdd(&cursor[o], 1)] = (int32_t)gi;
-}
-
-__global__ void k_i64_to_i32(const int64_t *__restrict__ a, int32_t *__restrict__ b, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = (int32_t)a[i];
 }
 
 // Bounds of the wrapped positions (needed along open axes only): per-block minima and maxima of
@@ -550,72 +502,114 @@ __global__ __launch_bounds__(256) void k_minmax(int nb, const double *__restrict
         for (int a = 0; a < 3; ++a) { out[a] = smin[a][0]; out[3 + a] = smax[a][0]; }
 }
 
-__global__ void k_xref(int64_t n, const double *__restrict__ pos, const int32_t *__restrict__ perm,
-                       double *__restrict__ xref) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int64_t u = perm[i];
-    for (int a = 0; a < 3; ++a) xref[3 * i + a] = pos[3 * u + a];
-}
-
 // ---------------------------------------------------------------------- scan --
 
-__global__ void k_scan_block(int64_t *__restrict__ d, int64_t n, int64_t *__restrict__ sums) {
-    __shared__ int64_t s[1024];
-    int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-    int64_t v = i < n ? d[i] : 0;
-    s[threadIdx.x] = v;
+// Exclusive scans of n counts (32- or 64-bit) into 64-bit offsets out[0 .. n], out[n] = total
+// (in and out may be the same array).  A thread takes kScanItems consecutive counts; the
+// block's threads are combined by shuffles and one LDS word per wave.  zero_in clears the
+// counts behind the scan (they are used as cursors next).
+constexpr int kScanThreads = 1024, kScanItems = 4, kScanTile = kScanThreads * kScanItems;
+
+// Exclusive prefix of v over the block (kScanThreads threads); total receives the block's sum.
+__device__ inline int64_t block_exclusive(int64_t v, int64_t &total) {
+    __shared__ int64_t s_wave[kScanThreads / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int64_t inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t t = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += t;
+    }
+    __syncthreads();   // the previous call's readers are done
+    if (lane == 63) s_wave[w] = inc;
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        int64_t t = (int)threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
+    int64_t before = 0, sum = 0;
+    for (int q = 0; q < kScanThreads / 64; ++q) {
+        const int64_t t = s_wave[q];
+        if (q < w) before += t;
+        sum += t;
     }
-    if (i < n) d[i] = s[threadIdx.x] - v;   // exclusive
-    if (threadIdx.x == 1023) sums[blockIdx.x] = s[1023];
+    total = sum;
+    return before + inc - v;
 }
 
-__global__ void k_scan_add(int64_t *__restrict__ d, int64_t n, const int64_t *__restrict__ sums) {
-    int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-    if (i < n) d[i] += sums[blockIdx.x];
-}
-
-static void scan_rec(hipStream_t st, int64_t *d, int64_t n, int64_t *tmp) {
-    int64_t nb = (n + 1023) / 1024;
-    int64_t *sums = tmp;
-    hipLaunchKernelGGL(k_scan_block, dim3((unsigned)nb), dim3(1024), 0, st, d, n, sums);
-    LAUNCH_OK("k_scan_block");
-    if (nb > 1) {
-        scan_rec(st, sums, nb, tmp + nb + 1);
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(1024), 0, st, d, n, sums);
-        LAUNCH_OK("k_scan_add");
+template <typename In>
+__device__ inline int64_t scan_tile(const In *in, int64_t *out, int64_t n, int64_t base, int64_t carry, In *zero_in) {
+    int64_t v[kScanItems], mine = 0;
+    const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
+#pragma unroll
+    for (int u = 0; u < kScanItems; ++u) {
+        v[u] = i0 + u < n ? (int64_t)in[i0 + u] : 0;
+        mine += v[u];
     }
-}
-
-// d holds n counts in [0, n); on return d[0..n] are exclusive offsets, d[n] = total.  Enqueued
-// only: the total stays on the device.
-static void scan_exclusive_async(hipStream_t st, int64_t *d, int64_t n, DevBuf &tmp) {
-    // last element + its count = total: scan n+1 values where d[n] was set to 0 by the caller
-    int64_t m = n + 1;
-    int64_t need = 0, k = m;
-    while (k > 1) { k = (k + 1023) / 1024; need += k + 1; }
-    int64_t *t = static_cast<int64_t *>(tmp.ensure((size_t)(need + 16) * sizeof(int64_t)));
-    scan_rec(st, d, m, t);
-}
-
-int64_t scan_exclusive_i64(hipStream_t st, int64_t *d, int64_t n, DevBuf &tmp) {
-    scan_exclusive_async(st, d, n, tmp);
-    int64_t total = 0;
-    HIP_OK(hipMemcpyAsync(&total, d + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_OK(hipStreamSynchronize(st));
+    int64_t total;
+    int64_t o = carry + block_exclusive(mine, total);
+#pragma unroll
+    for (int u = 0; u < kScanItems; ++u) {
+        if (i0 + u < n) {
+            out[i0 + u] = o;
+            if (zero_in) zero_in[i0 + u] = In(0);
+        }
+        o += v[u];
+    }
     return total;
 }
 
+// the whole scan in one block, tile after tile
+template <typename In>
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(const In *in, int64_t *out, int64_t n, In *zero_in) {
+    int64_t carry = 0;
+    for (int64_t base = 0; base < n; base += kScanTile) carry += scan_tile(in, out, n, base, carry, zero_in);
+    if (threadIdx.x == 0) out[n] = carry;
+}
+
+// one tile per block, its sum to sums[block]; k_scan_add then adds the scanned sums
+template <typename In>
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const In *in, int64_t *out, int64_t n, In *zero_in,
+                                                             int64_t *__restrict__ sums) {
+    const int64_t total = scan_tile(in, out, n, (int64_t)blockIdx.x * kScanTile, (int64_t)0, zero_in);
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_add(int64_t *__restrict__ out, int64_t n,
+                                                           const int64_t *__restrict__ sums) {
+    const int64_t add = sums[blockIdx.x];
+    const int64_t i0 = (int64_t)blockIdx.x * kScanTile + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kScanItems; ++u) {
+        const int64_t i = i0 + u * kScanThreads;
+        if (i < n) out[i] += add;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[gridDim.x];
+}
+
+// Up to kScanOne counts take one block (a tile is about 1 us, a launch about 3 us with its gap;
+// the 8,600 rows of a 3,000-atom box take 5.4 us in one block, 11 us in three launches), more take
+// the three launches.  Enqueued only: the total stays on the device.
+constexpr int64_t kScanOne = 4 * kScanTile;
+
+template <typename In>
+static void scan_exclusive_async(hipStream_t st, const In *in, int64_t *out, int64_t n, DevBuf &tmp,
+                                 In *zero_in = nullptr) {
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one<In>, dim3(1), dim3(kScanThreads), 0, st, in, out, n, zero_in);
+        LAUNCH_OK("k_scan_one");
+        return;
+    }
+    const int64_t nb = (n + kScanTile - 1) / kScanTile;
+    int64_t *sums = static_cast<int64_t *>(tmp.ensure((size_t)(nb + 1) * sizeof(int64_t)));
+    hipLaunchKernelGGL(k_scan_tiles<In>, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, out, n, zero_in, sums);
+    LAUNCH_OK("k_scan_tiles");
+    hipLaunchKernelGGL(k_scan_one<int64_t>, dim3(1), dim3(kScanThreads), 0, st, sums, sums, nb, (int64_t *)nullptr);
+    LAUNCH_OK("k_scan_one");
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, st, out, n, sums);
+    LAUNCH_OK("k_scan_add");
+}
+
 // Scattered device scalars the host needs (counts for allocation sizes, bounds, check flags),
-// gathered by one tiny kernel into one block and read with one copy: every read is a wait for
-// the stream, which behind other streams' work sharing a hardware queue can take far longer
-// than the work itself.
+// gathered by one tiny kernel into one block of pinned host memory and read after one wait for
+// the stream (behind other streams' work sharing a hardware queue a wait can take far longer
+// than the work itself).
 constexpr int kPickMax = 160;
 struct Pick {
     const void *p[kPickMax];
@@ -636,13 +630,22 @@ struct Picker {
         pk.is32[pk.n] = is32 ? 1 : 0;
         return pk.n++;
     }
-    // enqueue the gather, copy to `host` and wait
-    void read(hipStream_t st, DevBuf &dev, int64_t *host) {
-        int64_t *d = static_cast<int64_t *>(dev.ensure(kPickMax * sizeof(int64_t)));
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(128), 0, st, pk, d);
+    // enqueue the gather into pinned memory and wait; the values stay valid until the next read
+    const int64_t *read(hipStream_t st, NListScratch &s) {
+        if (current_arena()) {   // the allocation-free entry point: no pinned allocation, a copy instead
+            int64_t *d = static_cast<int64_t *>(s.chk.ensure(kPickMax * sizeof(int64_t)));
+            s.values.resize(kPickMax);
+            hipLaunchKernelGGL(k_pick, dim3(1), dim3(128), 0, st, pk, d);
+            LAUNCH_OK("k_pick");
+            HIP_OK(hipMemcpyAsync(s.values.data(), d, pk.n * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+            HIP_OK(hipStreamSynchronize(st));
+            return s.values.data();
+        }
+        int64_t *h = s.pick.get(kPickMax * sizeof(int64_t));
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(128), 0, st, pk, h);
         LAUNCH_OK("k_pick");
-        HIP_OK(hipMemcpyAsync(host, d, pk.n * sizeof(int64_t), hipMemcpyDeviceToHost, st));
         HIP_OK(hipStreamSynchronize(st));
+        return h;
     }
 };
 
@@ -663,12 +666,13 @@ void build_nlist(hipStream_t st, const double *d_pos, const int32_t *d_species, 
     int32_t *q = nl.q.resize(n * 3);
     int32_t *dom = static_cast<int32_t *>(s.b.ensure(n * sizeof(int32_t)));
     int64_t *goff = static_cast<int64_t *>(s.c.ensure((n + 1) * sizeof(int64_t)));
-    int32_t *bad = static_cast<int32_t *>(s.i.ensure(64));
-    HIP_OK(hipMemsetAsync(goff + n, 0, sizeof(int64_t), st));
-    HIP_OK(hipMemsetAsync(bad, 0, sizeof(int32_t), st));
+    // check flags: invalid positions, coincident copies, entries without their reverse
+    int32_t *flags = static_cast<int32_t *>(s.flag.ensure(64));
+    int32_t *bad = flags, *coinc = flags + 1, *asym = flags + 2;
+    HIP_OK(hipMemsetAsync(flags, 0, 64, st));
     hipLaunchKernelGGL(k_wrap_count, dim3(grid_for(n, B)), dim3(B), 0, st, g, n, d_pos, w, q, dom, goff, bad);
     LAUNCH_OK("k_wrap_count");
-    scan_exclusive_async(st, goff, n, s.m);
+    scan_exclusive_async(st, goff, goff, n, s.m);
     // the bounds of the wrapped locals set the bins along open axes only
     const bool open_axis = !(g.per[0] && g.per[1] && g.per[2]);
     double *d_mm = static_cast<double *>(s.mm.ensure((6 + 6 * kMinmaxBlocks) * sizeof(double)));
@@ -680,31 +684,25 @@ void build_nlist(hipStream_t st, const double *d_pos, const int32_t *d_species, 
         LAUNCH_OK("k_minmax");
     }
     // first read: ghost count, the invalid-position flag and (open axes) the bounds
-    int64_t hv[kPickMax];
     double bb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int64_t n_gh, any_bad;
     {
         Picker pk;
         pk.add(goff + n, false);
         pk.add(bad, true);
         if (open_axis)
             for (int a = 0; a < 6; ++a) pk.add(d_mm + a, false);
-        pk.read(st, s.chk, hv);
+        const int64_t *hv = pk.read(st, s);
+        n_gh = hv[0];
+        any_bad = hv[1];
         if (open_axis) std::memcpy(bb, hv + 2, sizeof bb);
     }
     check_deferred(s);   // a previous build's deferred check (the wait above covered its copy)
-    const int64_t n_gh = hv[0];
-    if (hv[1]) fail(REANN_E_INVALID, "positions contain NaN, Inf or |x| >= 1e9");
+    if (any_bad) fail(REANN_E_INVALID, "positions contain NaN, Inf or |x| >= 1e9");
     if (n + n_gh >= ((int64_t)1 << 31) - 1) fail(REANN_E_UNSUPPORTED, "extended system too large");
     nl.n_gh = n_gh;
     nl.n_ext = n + n_gh;
     const int64_t n_ext = nl.n_ext;
-    int32_t *g_owner = static_cast<int32_t *>(s.d.ensure((n_gh + 1) * sizeof(int32_t)));
-    int32_t *g_shift = static_cast<int32_t *>(s.e.ensure((n_gh + 1) * 3 * sizeof(int32_t)));
-    int32_t *g_dom = static_cast<int32_t *>(s.f.ensure((n_gh + 1) * sizeof(int32_t)));
-    double *g_pos = static_cast<double *>(s.g.ensure((n_gh + 1) * 3 * sizeof(double)));
-    hipLaunchKernelGGL(k_ghost_gen, dim3(grid_for(n, B)), dim3(B), 0, st, g, n, w, dom, goff, g_owner, g_shift, g_dom,
-                       g_pos);
-    LAUNCH_OK("k_ghost_gen");
 
     // spatial bins of size >= r_c + skin over the region holding every copy
     Bins b{};
@@ -725,20 +723,23 @@ void build_nlist(hipStream_t st, const double *d_pos, const int32_t *d_species, 
     const int64_t nkeys = (int64_t)(n_species + nghs) * g.ndom * b.nbin;
     if (nkeys > ((int64_t)1 << 28)) fail(REANN_E_UNSUPPORTED, "bin table too large");
 
+    int32_t *g_owner = static_cast<int32_t *>(s.d.ensure((n_gh + 1) * sizeof(int32_t)));
+    int32_t *g_shift = static_cast<int32_t *>(s.e.ensure((n_gh + 1) * 3 * sizeof(int32_t)));
+    int32_t *g_dom = static_cast<int32_t *>(s.f.ensure((n_gh + 1) * sizeof(int32_t)));
+    double *g_pos = static_cast<double *>(s.g.ensure((n_gh + 1) * 3 * sizeof(double)));
     int64_t *key = static_cast<int64_t *>(s.h.ensure(n_ext * sizeof(int64_t)));
     int32_t *cnt32 = static_cast<int32_t *>(s.i.ensure((nkeys + 1) * sizeof(int32_t)));
     int64_t *kstart = static_cast<int64_t *>(s.j.ensure((nkeys + 1) * sizeof(int64_t)));
-    HIP_OK(hipMemsetAsync(cnt32, 0, (nkeys + 1) * sizeof(int32_t), st));
+    hipLaunchKernelGGL(k_ghost_gen, dim3(grid_for(std::max(n, nkeys), B)), dim3(B), 0, st, g, n, w, dom, goff, g_owner,
+                       g_shift, g_dom, g_pos, cnt32, nkeys);
+    LAUNCH_OK("k_ghost_gen");
     hipLaunchKernelGGL(k_keys, dim3(grid_for(n_ext, B)), dim3(B), 0, st, b, g.ndom, n_species, n, n_gh, w, dom,
                        d_species, g_pos, g_dom, g_owner, ghosts_by_species ? 1 : 0, key, cnt32);
     LAUNCH_OK("k_keys");
-    hipLaunchKernelGGL(k_i32_to_i64, dim3(grid_for(nkeys + 1, B)), dim3(B), 0, st, cnt32, kstart, nkeys + 1);
-    LAUNCH_OK("k_i32_to_i64");
     // every ext atom adds one to exactly one key, so the total is n_ext by construction; it is
-    // read back (and checked) with the pair count below
-    scan_exclusive_async(st, kstart, nkeys, s.m);
+    // read back (and checked) with the pair count below.  The counts are cleared for the scatter.
+    scan_exclusive_async(st, cnt32, kstart, nkeys, s.m, cnt32);
     int32_t *order = static_cast<int32_t *>(s.k.ensure(n_ext * sizeof(int32_t)));
-    HIP_OK(hipMemsetAsync(cnt32, 0, (nkeys + 1) * sizeof(int32_t), st));
     hipLaunchKernelGGL(k_scatter, dim3(grid_for(n_ext, B)), dim3(B), 0, st, n_ext, key, kstart, cnt32, order);
     LAUNCH_OK("k_scatter");
     hipLaunchKernelGGL(k_sort_segments, dim3(grid_for(nkeys, 4)), dim3(256), 0, st, nkeys, kstart, order);
@@ -752,42 +753,30 @@ void build_nlist(hipStream_t st, const double *d_pos, const int32_t *d_species, 
     int32_t *gh_owner_user = static_cast<int32_t *>(s.gou.ensure((n_gh + 1) * sizeof(int32_t)));
     int8_t *spec_ext = nl.spec_ext.resize(n_ext);
     int32_t *gh_shift = nl.gh_shift.resize((n_gh + 1) * 3);
-    hipLaunchKernelGGL(k_build_ext, dim3(grid_for(n_ext, B)), dim3(B), 0, st, b, n, n_ext, order, w, dom, d_species,
-                       g_pos, g_dom, g_owner, g_shift, perm, inv_perm, pext, d_dom_ext, d_bin_ext, spec_ext,
-                       gh_owner_user, gh_shift);
-    LAUNCH_OK("k_build_ext");
     int32_t *gh_owner = nl.gh_owner.resize(n_gh + 1);
-    if (n_gh > 0) {
-        hipLaunchKernelGGL(k_ghost_owner, dim3(grid_for(n_gh, B)), dim3(B), 0, st, n_gh, gh_owner_user, inv_perm,
-                           gh_owner);
-        LAUNCH_OK("k_ghost_owner");
-    }
+    int2 *copy_rng = nl.copy_rng.resize(n);
+    int32_t *copy_idx = nl.copy_idx.resize(n_gh + 1);
+    double *xref = nl.xref.resize(n * 3);
+    hipLaunchKernelGGL(k_build_ext, dim3(grid_for(n_ext, B)), dim3(B), 0, st, b, n, n_ext, order, d_pos, w, dom,
+                       d_species, goff, g_pos, g_dom, g_owner, g_shift, perm, inv_perm, pext, d_dom_ext, d_bin_ext,
+                       spec_ext, gh_owner_user, gh_shift, copy_rng, copy_idx, xref);
+    LAUNCH_OK("k_build_ext");
 
     // rows: count (keeping the hits), scan, fill.  A bin holds about n_ext / nbin atoms (a
     // subdomain's atoms fill about its own share of the bins), so a row has about
-    // 27 n_ext / nbin candidates; the hits are kept for up to about twice that (as bits per
-    // candidate, or one word per 32-atom chunk of a key).  Keys of 24 or more atoms on average
-    // take a half-wave per row, smaller ones a thread per row.
+    // 27 n_ext / nbin candidates; the hits are kept for up to about twice that.
     int64_t *row = nl.row.resize(n_ext + 1);
-    HIP_OK(hipMemsetAsync(row + n_ext, 0, sizeof(int64_t), st));
-    int32_t *coinc = static_cast<int32_t *>(s.coinc.ensure(64));
-    HIP_OK(hipMemsetAsync(coinc, 0, sizeof(int32_t), st));
-    const double per_bin = (double)n_ext / (double)b.nbin, mean_cand = 27.0 * per_bin;
-    const bool group = per_bin / n_species >= 24.0;
-    const double words = std::ceil(2.0 * mean_cand / 32.0) + 2.0 + (group ? 27.0 * (n_species + nghs) : 0.0);
-    const int cap_words = (int)std::min<double>(4096.0, words);
+    const double mean_cand = 27.0 * (double)n_ext / (double)b.nbin;
+    const int cap_words = (int)std::min<double>(4096.0, std::ceil(2.0 * mean_cand / 32.0) + 2.0);
     uint32_t *mask = static_cast<uint32_t *>(s.mask.ensure((size_t)n_ext * cap_words * sizeof(uint32_t)));
     int32_t *nkept = static_cast<int32_t *>(s.ncand.ensure((size_t)n_ext * sizeof(int32_t)));
-    if (group)
-        hipLaunchKernelGGL(k_rows_group<false>, dim3(grid_for(n_ext, kRowsPerBlk)), dim3(256), 0, st, b, g, n_species,
-                           nghs, n, n_ext, pext, d_dom_ext, d_bin_ext, kstart, row, nullptr, nullptr, coinc, mask, nkept,
-                           cap_words);
-    else
-        hipLaunchKernelGGL(k_rows_thread<false>, dim3(grid_for(n_ext, 128)), dim3(128), 0, st, b, g, n_species, nghs, n,
-                           n_ext, pext, d_dom_ext, d_bin_ext, kstart, row, nullptr, nullptr, coinc, mask, nkept, cap_words);
+    hipLaunchKernelGGL(k_rows<false>, dim3(grid_for(n_ext, kRowsPerBlk)), dim3(256), 0, st, b, g, n_species, nghs, n,
+                       n_ext, pext, d_dom_ext, d_bin_ext, kstart, row, nullptr, nullptr, nullptr, coinc, mask, nkept,
+                       cap_words, gh_owner_user, inv_perm, gh_owner);
     LAUNCH_OK("k_rows<count>");
-    scan_exclusive_async(st, row, n_ext, s.m);
+    scan_exclusive_async(st, row, row, n_ext, s.m);
     // second read: pair counts, the key total and the species segments of the locals
+    int64_t n_pairs;
     {
         Picker pk;
         pk.add(row + n_ext, false);
@@ -797,87 +786,47 @@ void build_nlist(hipStream_t st, const double *d_pos, const int32_t *d_species, 
         for (int sp = 0; sp <= n_species; ++sp) pk.add(kstart + (int64_t)sp * g.ndom * b.nbin, false);
         if (ghosts_by_species)
             for (int sp = 1; sp <= n_species; ++sp) pk.add(kstart + (int64_t)(n_species + sp) * g.ndom * b.nbin, false);
-        pk.read(st, s.chk, hv);
-    }
-    const int64_t n_pairs = hv[0];
-    if (hv[2] != n_ext) fail(REANN_E_DEVICE, "neighbour build: key count mismatch");
-    if (hv[3]) fail(REANN_E_INVALID, "two atoms (or an atom and a periodic copy) closer than 1e-6 A");
-    nl.seg.assign(hv + 4, hv + 4 + n_species + 1);
-    // ghost species segments: [gseg[s], gseg[s+1]) are the ghosts of element s (ghosts_by_species),
-    // else one segment of every ghost
-    if (ghosts_by_species) {
-        nl.gseg.assign(1, n);
-        nl.gseg.insert(nl.gseg.end(), hv + 4 + n_species + 1, hv + 4 + 2 * n_species + 1);
-    } else {
-        nl.gseg = {n, n_ext};
+        const int64_t *hv = pk.read(st, s);
+        n_pairs = hv[0];
+        if (hv[2] != n_ext) fail(REANN_E_DEVICE, "neighbour build: key count mismatch");
+        if (hv[3]) fail(REANN_E_INVALID, "two atoms (or an atom and a periodic copy) closer than 1e-6 A");
+        nl.n_local_pairs = hv[1];
+        nl.seg.assign(hv + 4, hv + 4 + n_species + 1);
+        // ghost species segments: [gseg[s], gseg[s+1]) are the ghosts of element s
+        // (ghosts_by_species), else one segment of every ghost
+        if (ghosts_by_species) {
+            nl.gseg.assign(1, n);
+            nl.gseg.insert(nl.gseg.end(), hv + 4 + n_species + 1, hv + 4 + 2 * n_species + 1);
+        } else {
+            nl.gseg = {n, n_ext};
+        }
     }
     if (nl.gseg.back() != n_ext) fail(REANN_E_DEVICE, "neighbour build: ghost segments mismatch");
     if (nl.seg[n_species] != n) fail(REANN_E_DEVICE, "neighbour build: species segments mismatch");
     if (n_pairs >= ((int64_t)1 << 31) - 1) fail(REANN_E_UNSUPPORTED, "too many neighbour pairs");
     nl.n_pairs = n_pairs;
-    nl.n_local_pairs = hv[1];
     int32_t *col = nl.col.resize(n_pairs + 1);
-    if (group)
-        hipLaunchKernelGGL(k_rows_group<true>, dim3(grid_for(n_ext, kRowsPerBlk)), dim3(256), 0, st, b, g, n_species,
-                           nghs, n, n_ext, pext, d_dom_ext, d_bin_ext, kstart, nullptr, row, col, nullptr, mask, nkept,
-                           cap_words);
-    else
-        hipLaunchKernelGGL(k_rows_thread<true>, dim3(grid_for(n_ext, 128)), dim3(128), 0, st, b, g, n_species, nghs, n,
-                           n_ext, pext, d_dom_ext, d_bin_ext, kstart, nullptr, row, col, nullptr, mask, nkept, cap_words);
+    int32_t *rev = nl.rev.resize(n_pairs + 1);
+    hipLaunchKernelGGL(k_rows<true>, dim3(grid_for(n_ext, kRowsPerBlk)), dim3(256), 0, st, b, g, n_species, nghs, n,
+                       n_ext, pext, d_dom_ext, d_bin_ext, kstart, nullptr, row, col, rev, nullptr, mask, nkept,
+                       cap_words, nullptr, nullptr, nullptr);
     LAUNCH_OK("k_rows<fill>");
     // the rows are ascending as filled; the reverse slot of every entry
-    {
-        int32_t *rev = nl.rev.resize(n_pairs + 1);
-        int32_t *flag = static_cast<int32_t *>(s.flag.ensure(64));
-        HIP_OK(hipMemsetAsync(flag, 0, sizeof(int32_t), st));
-        HIP_OK(hipMemsetAsync(rev, 0xff, (n_pairs + 1) * sizeof(int32_t), st));   // -1: not resolved
-        hipLaunchKernelGGL(k_reverse, dim3(grid_for(n_ext * 16, B)), dim3(B), 0, st, n_ext, row, col, rev, flag);
-        LAUNCH_OK("k_reverse");
-        if (n_pairs > 0) {
-            hipLaunchKernelGGL(k_reverse_check, dim3(grid_for(n_pairs, B)), dim3(B), 0, st, n_pairs, rev, flag);
-            LAUNCH_OK("k_reverse_check");
-        }
+    hipLaunchKernelGGL(k_reverse, dim3(grid_for(n_ext * 16, B)), dim3(B), 0, st, n_ext, row, col, rev, asym);
+    LAUNCH_OK("k_reverse");
+    if (n_pairs > 0) {
+        hipLaunchKernelGGL(k_reverse_check, dim3(grid_for(n_pairs, B)), dim3(B), 0, st, n_pairs, rev, asym);
+        LAUNCH_OK("k_reverse_check");
     }
-
-    // owner -> ghost copies
-    int32_t *copy_ptr = nl.copy_ptr.resize(n + 1);
-    int32_t *copy_idx = nl.copy_idx.resize(n_gh + 1);
-    {
-        int32_t *c32 = static_cast<int32_t *>(s.i.ensure((n + 1) * sizeof(int32_t)));
-        int64_t *c64 = static_cast<int64_t *>(s.j.ensure((n + 1) * sizeof(int64_t)));
-        HIP_OK(hipMemsetAsync(c32, 0, (n + 1) * sizeof(int32_t), st));
-        if (n_gh > 0) {
-            hipLaunchKernelGGL(k_copy_count, dim3(grid_for(n_gh, B)), dim3(B), 0, st, n_gh, gh_owner, c32);
-            LAUNCH_OK("k_copy_count");
-        }
-        hipLaunchKernelGGL(k_i32_to_i64, dim3(grid_for(n + 1, B)), dim3(B), 0, st, c32, c64, n + 1);
-        LAUNCH_OK("k_i32_to_i64");
-        scan_exclusive_async(st, c64, n, s.m);
-        hipLaunchKernelGGL(k_i64_to_i32, dim3(grid_for(n + 1, B)), dim3(B), 0, st, c64, copy_ptr, n + 1);
-        LAUNCH_OK("k_i64_to_i32");
-        if (n_gh > 0) {
-            HIP_OK(hipMemsetAsync(c32, 0, (n + 1) * sizeof(int32_t), st));
-            hipLaunchKernelGGL(k_copy_fill, dim3(grid_for(n_gh, B)), dim3(B), 0, st, n_gh, gh_owner, c64, c32, copy_idx);
-            LAUNCH_OK("k_copy_fill");
-            hipLaunchKernelGGL(k_sort_segments32, dim3(grid_for(n, B)), dim3(B), 0, st, n, copy_ptr, copy_idx);
-            LAUNCH_OK("k_sort_segments32");
-        }
-    }
-    double *xref = nl.xref.resize(n * 3);
-    hipLaunchKernelGGL(k_xref, dim3(grid_for(n, B)), dim3(B), 0, st, n, d_pos, perm, xref);
-    LAUNCH_OK("k_xref");
     // last read (the list is complete when it returns): the symmetry check of the reverse slots
     if (defer_check) {
-        HIP_OK(hipMemcpyAsync(s.sym.get(), s.flag.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        HIP_OK(hipMemcpyAsync(s.sym.get(), asym, sizeof(int32_t), hipMemcpyDeviceToHost, st));
         s.sym_pending = true;
         return;
     }
-    {
-        Picker pk;
-        pk.add(s.flag.p, true);
-        pk.read(st, s.chk, hv);
-    }
-    if (hv[0]) fail(REANN_E_DEVICE, "neighbour build: list is not symmetric");
+    Picker pk;
+    pk.add(asym, true);
+    if (pk.read(st, s)[0]) fail(REANN_E_DEVICE, "neighbour build: list is not symmetric");
 }
 
 void check_deferred(NListScratch &s) {

@@ -37,8 +37,8 @@ struct NList {
     DArr<int32_t> q;             // [n*3] integer wrap per axis, caller order: w = x - q L
     DArr<int32_t> gh_owner;      // [n_gh] local index of the owner
     DArr<int32_t> gh_shift;      // [n_gh*3] lattice shift of the copy
-    DArr<int32_t> copy_ptr;      // [n+1]  owner -> its ghost copies (CSR)
-    DArr<int32_t> copy_idx;      // [n_gh] ghost indices in increasing order per owner
+    DArr<int2> copy_rng;         // [n]    owner -> its ghost copies: copy_idx[x .. y)
+    DArr<int32_t> copy_idx;      // [n_gh] ghost indices, per owner in the order (shift, subdomain)
     DArr<int64_t> row;           // [n_ext+1]
     DArr<int32_t> col;           // [n_pairs] ext indices
     DArr<int32_t> rev;           // [n_pairs] slot of the reverse entry (j -> x) of entry (x -> j)
@@ -48,7 +48,9 @@ struct NList {
 
 // Scratch reused between builds.
 struct NListScratch {
-    DevBuf a, b, c, d, e, f, g, h, i, j, k, l, m, flag, mm, chk, dext, bext, gou, coinc, mask, ncand;
+    DevBuf a, b, c, d, e, f, g, h, i, j, k, l, m, flag, mm, chk, dext, bext, gou, mask, ncand;
+    PinnedWords pick;           // values the host reads during a build
+    std::vector<int64_t> values;   // the same without pinned memory
     PinnedWord sym;             // deferred symmetry check: the flag, copied back
     bool sym_pending = false;
 };
@@ -64,9 +66,6 @@ void build_nlist(hipStream_t st, const double *d_pos, const int32_t *d_species, 
                  bool defer_check = false);
 // REANN_E_DEVICE if a deferred check failed (the stream of the build must have been waited for).
 void check_deferred(NListScratch &s);
-
-// Exclusive scan of n int64 values in place; returns the total (synchronises).
-int64_t scan_exclusive_i64(hipStream_t st, int64_t *d, int64_t n, DevBuf &tmp);
 
 // Positions of the extended system from caller positions: w_i = x_{perm i} - q_i L for
 // locals, owner position + shift L for ghosts.  SoA output px/py/pz [n_ext].

@@ -326,7 +326,7 @@ size_t Plan::device_bytes() const {
                             &fp8tmp, &cbar_next})
         b += d->bytes;
     b += nl.perm.bytes() + nl.inv_perm.bytes() + nl.q.bytes() + nl.gh_owner.bytes() + nl.gh_shift.bytes() +
-         nl.copy_ptr.bytes() + nl.copy_idx.bytes() + nl.row.bytes() + nl.col.bytes() + nl.rev.bytes() + nl.spec_ext.bytes() +
+         nl.copy_rng.bytes() + nl.copy_idx.bytes() + nl.row.bytes() + nl.col.bytes() + nl.rev.bytes() + nl.spec_ext.bytes() +
          nl.xref.bytes() + d_species.bytes();
     return b;
 }
@@ -760,7 +760,7 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
             // node-feature exchange: the ghosts keep theirs (their message NN ran locally) and
             // the adjoints of their orbital sums go back after the NN's VJP
             if (!nodefeat) {
-                ghost_reduce(st, fp64, n, K, nl.copy_ptr.ptr(), nl.copy_idx.ptr(), cbar.p);
+                ghost_reduce(st, fp64, n, K, nl.copy_rng.ptr(), nl.copy_idx.ptr(), cbar.p);
                 mark(st, PH_GHOST);
             }
             if (radial()) {   // c^t also reaches E through c^{t+1} = c^t + NN(x^t) (t < T - 1)
@@ -777,12 +777,12 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
                 mark(st, PH_DENSITY_ADJ, 1);
             }
             if (nodefeat) {   // the ghosts' dE/dS^{t-1} summed onto their owners
-                ghost_reduce(st, fp64, n, m->NL * K, nl.copy_ptr.ptr(), nl.copy_idx.ptr(), Sbar.p);
+                ghost_reduce(st, fp64, n, m->NL * K, nl.copy_rng.ptr(), nl.copy_idx.ptr(), Sbar.p);
                 mark(st, PH_GHOST);
             }
         }
     }
-    ghost_reduce(st, fp64, n, 3, nl.copy_ptr.ptr(), nl.copy_idx.ptr(), this->F.p);
+    ghost_reduce(st, fp64, n, 3, nl.copy_rng.ptr(), nl.copy_idx.ptr(), this->F.p);
     mark(st, PH_GHOST);
     // the seed carried g; forces are -dE/dx already scaled; the virial partials are summed in the
     // same launch
