@@ -238,14 +238,47 @@ void convert_operand(hipStream_t st, OpType op, const float *src, int rows, int 
     LAUNCH_OK("k_convert");
 }
 
+template <OpType OP>
+__global__ void k_pack(const float *__restrict__ src, int rows, int cols, int ld_src, typename OpT<OP>::T *dst,
+                       int nblk, int64_t total, const float *__restrict__ scale) {
+    constexpr int RUN = op_run(OP), KC = 4 * RUN;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= total) return;
+    const int e = (int)(t % RUN), lane = (int)(t / RUN % 64);
+    const int64_t f = t / (RUN * 64);
+    const int r = (int)(f % nblk) * 16 + lane % 16;
+    const int64_t c = f / nblk * KC + RUN * (lane / 16) + e;
+    const float inv = (OP == OpType::FP8) ? 1.0f / scale[0] : 1.0f;
+    dst[t] = r < rows && c < cols ? to_op<OP>(src[(int64_t)r * ld_src + c], inv) : typename OpT<OP>::T(0);
+}
+
+void pack_operand(hipStream_t st, OpType op, const float *src, int rows, int cols, int ld_src, void *dst,
+                  const float *scale) {
+    const int64_t tot = (int64_t)packed_elems(op, rows, cols);
+    const int nblk = (rows + 15) / 16;
+    if (tot == 0) return;
+    const dim3 grid(grid_for(tot, 256)), block(256);
+    if (op == OpType::F32)
+        hipLaunchKernelGGL(k_pack<OpType::F32>, grid, block, 0, st, src, rows, cols, ld_src, (float *)dst, nblk, tot, scale);
+    else if (op == OpType::BF16)
+        hipLaunchKernelGGL(k_pack<OpType::BF16>, grid, block, 0, st, src, rows, cols, ld_src, (uint16_t *)dst, nblk, tot, scale);
+    else
+        hipLaunchKernelGGL(k_pack<OpType::FP8>, grid, block, 0, st, src, rows, cols, ld_src, (uint8_t *)dst, nblk, tot, scale);
+    LAUNCH_OK("k_pack");
+}
+
 // ------------------------------------------------------- fused atomic NNs --
 //
-// One workgroup takes kFuseBM rows of one element's NN through every layer; the activations
-// stay in LDS between layers and only the pre-activations Z_k (needed by the adjoint) and
-// the outputs reach HBM.  Each of the 4 waves owns every row of the tile and the column
-// blocks j = wave + 4 jj of the layer output; its weight fragments come straight from
-// global memory (every tile reads the same weights, so they stay in cache) one K chunk
-// ahead of the matrix instructions.
+// One workgroup of NW waves takes BM rows of one element's NN through every layer; the
+// activations stay in LDS between layers and only the pre-activations Z_k (needed by the
+// adjoint) and the outputs reach HBM.  Each wave owns every row of the tile and the column
+// blocks j = wave + NW jj of the layer output; its weight fragments come straight from
+// global memory (every tile reads the same weights, so they stay in cache) ahead of the matrix
+// instructions.  The weights are stored in the order the fragments are read (packed_elems), so
+// that a fragment load of a wave is one contiguous block of 1 KB (FP8: 512 B): as rows, it
+// touched 16 lines and used half of each (forward / adjoint of the 100,800-atom crystal: FP32
+// 157 / 182 -> 155 / 160 us, now held by the matrix and vector instructions of a SIMD, which do not
+// overlap here; BF16 95 / 100 -> 72 / 70 us; 1.2M-atom water, H = 64, FP32 471 / 497 -> 430 / 435).
 //
 // Operand order inside a K chunk: lane l (row or column l % 16, group g = l / 16) holds a
 // contiguous run of k; for FP32 the run is 4 long and sub-step s of the chunk uses element s,
@@ -254,14 +287,10 @@ void convert_operand(hipStream_t st, OpType op, const float *src, int rows, int 
 
 namespace {
 
-constexpr int kFuseWaves = 4;
-constexpr int kOutParts = 8;   // threads per row in the output layer (kFuseBM * kOutParts = 256)
-static_assert(kFuseBM * kOutParts == 256, "output layer mapping");
-
 template <OpType OP> struct Fuse;
 template <> struct Fuse<OpType::F32> {
     using T = float;
-    static constexpr int KC = 16;    // k per chunk
+    static constexpr int KC = 16;    // k per chunk (4 op_run)
     static constexpr int PAD = 4;    // LDS row padding (elements): row stride = 4 banks mod 64
 };
 template <> struct Fuse<OpType::BF16> {
@@ -294,34 +323,40 @@ template <int CTRL> __device__ inline float dpp_f32(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-// Sum over each group of 8 consecutive lanes (every lane gets the same value: the quad sums
-// are formed in the same order everywhere and the last step adds two of them, which
-// commutes exactly).
-template <typename A> __device__ inline A sum8(A v) {
-    if constexpr (sizeof(A) == 8) {
-        v += dpp_f64<kDppXor1>(v);
-        v += dpp_f64<kDppXor2>(v);
-        return v + dpp_f64<kDppHalfMirror>(v);
-    } else {
-        v += dpp_f32<kDppXor1>(v);
-        v += dpp_f32<kDppXor2>(v);
-        return v + dpp_f32<kDppHalfMirror>(v);
-    }
+template <int CTRL> __device__ inline double dpp_any(double v) { return dpp_f64<CTRL>(v); }
+template <int CTRL> __device__ inline float dpp_any(float v) { return dpp_f32<CTRL>(v); }
+constexpr int kDppMirror = 0x140;      // lane i <- lane 15 - i within each row of 16
+
+// Sum over each group of N = 8, 16 or 32 consecutive lanes (every lane gets the same value: each
+// step adds the two halves' sums, which commutes exactly).
+template <int N, typename A> __device__ inline A sum_lanes(A v) {
+    static_assert(N == 8 || N == 16 || N == 32, "lane group");
+    v += dpp_any<kDppXor1>(v);
+    v += dpp_any<kDppXor2>(v);
+    v += dpp_any<kDppHalfMirror>(v);
+    if constexpr (N >= 16) v += dpp_any<kDppMirror>(v);
+    if constexpr (N == 32) v += __shfl_xor(v, 16, 64);
+    return v;
 }
 
-// Output layer of the forward (FP32 data, accumulation in A): kOutParts threads share a row,
-// each takes H / kOutParts hidden units for all DOUT outputs, and the partial sums are
-// combined across the row's threads; thread `part` writes outputs part, part + kOutParts, ...
+// Register sets of weight fragments: chunks requested ahead of the one being multiplied, plus it.
+// 2, 3 and 4 sets take 14.9, 13.7 and 13.6 us for the 4,000-atom forward (FP32); large launches
+// do not tell them apart.
+template <int NCB, int NCK> constexpr int fuse_depth() { return NCK < 3 ? (NCK < 2 ? 1 : 2) : 3; }
+
+// Output layer of the forward (FP32 data, accumulation in A): PARTS threads share a row, each
+// takes H / PARTS hidden units for all DOUT outputs, and the partial sums are combined across the
+// row's threads; thread `part` writes outputs part, part + PARTS, ...
 // The energy NN (one output) accumulates in FP64 with FP64 weights and bias: its output is a
 // sum of H terms that can cancel to a small atomic energy, so the FP32 rounding of its weights
 // would be amplified by that cancellation.  The message NNs accumulate in FP32 with FP32 weights,
 // like their hidden layers.  H (the hidden width) is a compile-time constant, so the loops
 // unroll without branches.
-template <int DOUT, typename A, int H, typename WT>
+template <int DOUT, typename A, int H, int PARTS, typename WT>
 __device__ inline void out_layer(const float *hl, int ldl, const WT *wo, const WT *bo, const FusedNN &p, int64_t m0,
                                  int tid) {
-    constexpr int QN = H / kOutParts;
-    const int row = tid / kOutParts, part = tid % kOutParts;
+    constexpr int QN = H / PARTS;
+    const int row = tid / PARTS, part = tid % PARTS;
     A hv[QN];
 #pragma unroll
     for (int j = 0; j < QN; ++j) hv[j] = (A)hl[row * ldl + part * QN + j];
@@ -335,46 +370,43 @@ __device__ inline void out_layer(const float *hl, int ldl, const WT *wo, const W
         s[o] = a;
     }
 #pragma unroll
-    for (int o = 0; o < DOUT; ++o) s[o] = sum8(s[o]);
+    for (int o = 0; o < DOUT; ++o) s[o] = sum_lanes<PARTS>(s[o]);
     const int64_t grow = m0 + row;
     if (grow < p.rows) {
 #pragma unroll
         for (int o = 0; o < DOUT; ++o)
-            if (o % kOutParts == part) p.C[grow * p.ldc + o] = (float)(s[o] + (A)bo[o]);
+            if (o % PARTS == part) p.C[grow * p.ldc + o] = (float)(s[o] + (A)bo[o]);
     }
 }
 
-// acc[rb][cb] = sum_k X[16 rb + i][k] Wt[16 (wave + 4 cb) + j][k] over k < kin (a multiple of
-// the chunk).  Columns at or past `out` read row 0 of Wt; the caller never stores them.
-template <OpType OP, int NCB, bool SPLIT>
-__device__ inline void fused_layer(const typename Fuse<OP>::T *X, int ldx, const typename Fuse<OP>::T *__restrict__ Wt,
-                                   int ldw, int kin, int out, int wave, int lane, f4 (&acc)[kFuseBM / 16][NCB]) {
-    constexpr int RB = kFuseBM / 16, KC = Fuse<OP>::KC;
+// acc[rb][cb] = sum_k X[16 rb + i][k] W[16 (wave + NW cb) + j][k] over NCK chunks of k, W packed
+// with NBLK column blocks.  Blocks at or past NBLK read the last one; the caller never stores
+// them.
+template <OpType OP, int RB, int NCB, int NW, int NCK, int NBLK, bool SPLIT>
+__device__ inline void fused_layer(const typename Fuse<OP>::T *X, int ldx, const void *__restrict__ W, int wave,
+                                   int lane, f4 (&acc)[RB][NCB]) {
+    using T = typename Fuse<OP>::T;
+    using V = typename std::conditional<OP == OpType::F32, fl4,
+                                        typename std::conditional<OP == OpType::BF16, u16x8, long>::type>::type;
+    constexpr int KC = Fuse<OP>::KC, RUN = op_run(OP);
+    constexpr int NS = fuse_depth<NCB, NCK>();   // register sets of weight fragments
     const int li = lane & 15, lg = lane >> 4;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
-    const typename Fuse<OP>::T *wrow[NCB];
+    uint32_t woff[NCB];   // bytes from the chunk's first fragment
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-        const int col = 16 * (wave + kFuseWaves * cb) + li;
-        wrow[cb] = Wt + (size_t)(col < out ? col : 0) * ldw;
-    }
-    // weight fragments in two register sets used in turn: the set for chunk k0 + KC is
-    // requested before the matrix instructions of chunk k0 are issued (the scheduling
-    // barriers keep the compiler from moving the requests next to their use)
-    using T = typename Fuse<OP>::T;
-    using V = typename std::conditional<OP == OpType::F32, fl4,
-                                        typename std::conditional<OP == OpType::BF16, u16x8, long>::type>::type;
-    constexpr int RUN = OP == OpType::F32 ? 4 : 8;   // k per lane per chunk
-    auto load_b = [&](V (&b)[NCB], int k0) {
+    for (int cb = 0; cb < NCB; ++cb) woff[cb] = (uint32_t)(min(wave + NW * cb, NBLK - 1) * 64 + lane) * sizeof(V);
+    auto load_b = [&](V (&b)[NCB], int kc) {
+        const char *Wk = static_cast<const char *>(W) + (size_t)kc * (NBLK * 64 * sizeof(V));
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) b[cb] = *reinterpret_cast<const V *>(wrow[cb] + k0 + RUN * lg);
+        for (int cb = 0; cb < NCB; ++cb) b[cb] = *reinterpret_cast<const V *>(Wk + woff[cb]);
     };
-    auto load_a = [&](V (&a)[RB], int k0) {
+    auto load_a = [&](V (&a)[RB], int kc) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) a[rb] = *reinterpret_cast<const V *>(X + (16 * rb + li) * ldx + k0 + RUN * lg);
+        for (int rb = 0; rb < RB; ++rb)
+            a[rb] = *reinterpret_cast<const V *>(X + (16 * rb + li) * ldx + kc * KC + RUN * lg);
     };
     // SPLIT (the forward, whose rounding reaches the energy): even chunks accumulate into acc,
     // odd chunks into acc2, summed at the end, so each FP32 accumulation chain is half as long.
@@ -385,7 +417,6 @@ __device__ inline void fused_layer(const typename Fuse<OP>::T *X, int ldx, const
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) acc2[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
-    f4 (&accb)[RB][NCB] = SPLIT ? acc2 : acc;
     auto mma = [&](f4 (&c)[RB][NCB], const V (&a)[RB], const V (&b)[NCB]) {
         if constexpr (OP == OpType::F32) {
 #pragma unroll
@@ -410,30 +441,26 @@ __device__ inline void fused_layer(const typename Fuse<OP>::T *X, int ldx, const
                     c[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a[rb], b[cb], c[rb][cb], 0, 0, 0);
         }
     };
-    // pairs of chunks per trip, so that a trip is one basic block and the requests cannot be
-    // sunk into a later block next to their use; both operands of chunk k0 + KC (weights from
-    // global memory, the activation tile from LDS) are requested before chunk k0 is multiplied
-    V a0[RB], a1[RB], b0[NCB], b1[NCB];
-    const int nck = kin / KC, klast = kin - KC;
-    load_b(b0, 0);
-    load_a(a0, 0);
-    int k0 = 0;
-    for (int pr = 0; pr + 2 <= nck; pr += 2) {
-        load_b(b1, k0 + KC);
-        load_a(a1, k0 + KC);
+    // NS sets of weight fragments and two of activation fragments in turn: the weights of chunk
+    // kc + NS - 1 and the activations of chunk kc + 1 are requested before chunk kc is
+    // multiplied (the scheduling barriers keep the compiler from moving the requests next to
+    // their use).  The chunk count is a compile-time constant, so the loop unrolls and every set
+    // is named statically.
+    V a[2][RB], b[NS][NCB];
+#pragma unroll
+    for (int q = 0; q < NS - 1; ++q)
+        if (q < NCK) load_b(b[q], q);
+    load_a(a[0], 0);
+#pragma unroll
+    for (int kc = 0; kc < NCK; ++kc) {
+        if (kc + NS - 1 < NCK) load_b(b[(kc + NS - 1) % NS], kc + NS - 1);
+        if (kc + 1 < NCK) load_a(a[(kc + 1) & 1], kc + 1);
         __builtin_amdgcn_sched_barrier(0);
-        mma(acc, a0, b0);
+        if (SPLIT && (kc & 1)) mma(acc2, a[kc & 1], b[kc % NS]);
+        else mma(acc, a[kc & 1], b[kc % NS]);
         __builtin_amdgcn_sched_barrier(0);
-        const int k2 = min(k0 + 2 * KC, klast);
-        load_b(b0, k2);
-        load_a(a0, k2);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(accb, a1, b1);
-        __builtin_amdgcn_sched_barrier(0);
-        k0 += 2 * KC;
     }
-    if (nck & 1) mma(acc, a0, b0);   // a0, b0 hold the last chunk
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT && NCK > 1) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -476,76 +503,90 @@ __device__ inline void density_part(const FusedNN &p, typename Fuse<OP>::T *X, i
         }
 }
 
-// Split of the pairs a <= b of K channels into a < A and a >= A with about half on each side.
-constexpr int pair_split(int K) {
+// The channel A such that the pairs a <= b with a < A are about num / den of all.
+constexpr int pair_split(int K, int num, int den) {
     int A = 0, n = 0;
-    while (2 * n < K * (K + 1) / 2) n += K - A++;
+    while (den * n < num * (K * (K + 1) / 2)) n += K - A++;
     return A;
 }
 
+// Features of the NN input (L = 0: the radial form's K sums), and their chunks.
+constexpr int fused_features(int L, int K) { return L == 0 ? K : n_feat(L, K); }
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
 // Forward of one element's NN over rows [0, rows): C = out_layer(SiLU(... SiLU(rho W_0^T + b_0) ...))
-// with rho the density of S.  NCB = H / 64 column blocks per wave; (L, K) fix the density.
+// with rho the density of S.  H (the hidden width) and (L, K) are compile-time constants.
 // L = 0 is the radial message form: its features are the K orbital sums S[0] themselves.
-template <OpType OP, int NCB, int L, int K>
+template <OpType OP, int H, int L, int K, int BM, int NW>
 __device__ __forceinline__ void mlp_fwd_body(const FusedNN &p, const int64_t m0) {
     using T = typename Fuse<OP>::T;
-    constexpr int BM = kFuseBM, RB = BM / 16;
-    constexpr int NLK = n_lambda(L) * K, P = K * (K + 1) / 2;
+    constexpr int RB = BM / 16, NT = NW * 64, NCB = H / 16 / NW, KC = Fuse<OP>::KC;
+    constexpr int F = fused_features(L, K), NCK0 = ceil_div(F, KC), Fk = NCK0 * KC;
+    static_assert(NCB >= 1 && NCB * NW * 16 == H, "column blocks per wave");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
-    // layer 0 contracts over F rounded up to the chunk size only (the weight rows are padded
-    // further, with zeros, which the product does not need)
-    const int F = p.F, H = p.H, Fk = (F + Fuse<OP>::KC - 1) / Fuse<OP>::KC * Fuse<OP>::KC;
-    const int ldx = (Fk > H ? Fk : H) + Fuse<OP>::PAD, ldf = H + 4;
+    // layer 0 contracts over F rounded up to the chunk size
+    constexpr int ldx = (Fk > H ? Fk : H) + Fuse<OP>::PAD, ldf = H + 4;
     // LDS, addressed from `smem` by offset arithmetic only (a pointer picked from an array
     // would lose its address space and turn every LDS access into a flat one): X [BM][ldx]
     // holds the layer-0 input and then, in place, every hidden layer's output; non-FP32
     // operands add an FP32 copy of the last hidden layer; W_out [dout][H].  One region for
     // the activations keeps four workgroups per CU.
-    const int offf = BM * ldx * (int)sizeof(T);
-    const int offw = offf + (OP == OpType::F32 ? 0 : BM * ldf * 4);
+    constexpr int offf = BM * ldx * (int)sizeof(T);
+    constexpr int offw = offf + (OP == OpType::F32 ? 0 : BM * ldf * 4);
     T *X = reinterpret_cast<T *>(smem);
     float *hf = reinterpret_cast<float *>(smem + offf);
     float *wo = reinterpret_cast<float *>(smem + offw);
     double *wo64 = reinterpret_cast<double *>(smem + offw);   // the energy NN's FP64 W_out instead
     if (p.dout == 1)
-        for (int e = tid; e < H; e += 256) wo64[e] = p.Wout64[e];
+        for (int e = tid; e < H; e += NT) wo64[e] = p.Wout64[e];
     else
-        for (int e = tid; e < p.dout * H; e += 256) wo[e] = p.Wout[e];
+        for (int e = tid; e < p.dout * H; e += NT) wo[e] = p.Wout[e];
     // layer-0 input: the density of this tile's orbital sums, rounded to the operand type and
-    // zero padded to Fk columns.  One task per wave (lanes 0..31 take the tile's rows): the
-    // orders l < L whole, and order L (the most components) split in two halves of its pairs,
-    // so that no wave runs divergent code and the longest task is about half of order L.
-    // The radial form (L = 0) copies the sums.
+    // zero padded to Fk columns.  One task per wave (lanes 0..BM-1 take the tile's rows): the
+    // orders l < L whole, and order L (the most components) split in parts of its pairs, so that
+    // no wave runs divergent code.  The radial form (L = 0) copies the sums.
     static_assert(L <= 2, "density tasks are laid out for L <= 2");
     if constexpr (L == 0) {
-        for (int it = tid; it < BM * K; it += 256) {
+        for (int it = tid; it < BM * K; it += NT) {
             const int r = it / K, f = it % K;
             const int64_t row = min(m0 + r, p.rows - 1);
             X[r * ldx + f] = to_op<OP>(p.S[row * K + f], OP == OpType::FP8 ? p.xinv[f] : 1.0f);
         }
     } else if (lane < BM) {
-        constexpr int AS = pair_split(K);
-        if (wave == 0) density_part<OP, L, K, 0, 0, (L == 1 ? K : K)>(p, X, ldx, m0, lane);
-        if constexpr (L == 2) {
+        constexpr int A1 = pair_split(K, 1, 2), B1 = pair_split(K, 1, 5), B2 = pair_split(K, 2, 5),
+                      B3 = pair_split(K, 3, 5), B4 = pair_split(K, 4, 5);
+        if constexpr (L == 2 && NW == 8) {
+            if (wave == 0) density_part<OP, L, K, 0, 0, K>(p, X, ldx, m0, lane);
+            if (wave == 1) density_part<OP, L, K, 1, 0, A1>(p, X, ldx, m0, lane);
+            if (wave == 2) density_part<OP, L, K, 1, A1, K>(p, X, ldx, m0, lane);
+            if (wave == 3) density_part<OP, L, K, 2, 0, B1>(p, X, ldx, m0, lane);
+            if (wave == 4) density_part<OP, L, K, 2, B1, B2>(p, X, ldx, m0, lane);
+            if (wave == 5) density_part<OP, L, K, 2, B2, B3>(p, X, ldx, m0, lane);
+            if (wave == 6) density_part<OP, L, K, 2, B3, B4>(p, X, ldx, m0, lane);
+            if (wave == 7) density_part<OP, L, K, 2, B4, K>(p, X, ldx, m0, lane);
+        } else if constexpr (L == 2) {
+            if (wave == 0) density_part<OP, L, K, 0, 0, K>(p, X, ldx, m0, lane);
             if (wave == 1) density_part<OP, L, K, 1, 0, K>(p, X, ldx, m0, lane);
-            if (wave == 2) density_part<OP, L, K, 2, 0, AS>(p, X, ldx, m0, lane);
-            if (wave == 3) density_part<OP, L, K, 2, AS, K>(p, X, ldx, m0, lane);
+            if (wave == 2) density_part<OP, L, K, 2, 0, A1>(p, X, ldx, m0, lane);
+            if (wave == 3) density_part<OP, L, K, 2, A1, K>(p, X, ldx, m0, lane);
         } else {
-            if (wave == 1) density_part<OP, L, K, 1, 0, AS>(p, X, ldx, m0, lane);
-            if (wave == 2) density_part<OP, L, K, 1, AS, K>(p, X, ldx, m0, lane);
+            if (wave == 0) density_part<OP, L, K, 0, 0, K>(p, X, ldx, m0, lane);
+            if (wave == 1) density_part<OP, L, K, 1, 0, A1>(p, X, ldx, m0, lane);
+            if (wave == 2) density_part<OP, L, K, 1, A1, K>(p, X, ldx, m0, lane);
         }
     }
-    for (int it = tid; it < BM * (Fk - F); it += 256)
-        X[(it / (Fk - F)) * ldx + F + it % (Fk - F)] = to_op<OP>(0.0f, 1.0f);
+    if constexpr (Fk > F)
+        for (int it = tid; it < BM * (Fk - F); it += NT)
+            X[(it / (Fk - F)) * ldx + F + it % (Fk - F)] = to_op<OP>(0.0f, 1.0f);
     __syncthreads();
     for (int k = 0; k < p.nh; ++k) {
         float bias[NCB];
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) bias[cb] = p.b[k][16 * (wave + kFuseWaves * cb) + li];
+        for (int cb = 0; cb < NCB; ++cb) bias[cb] = p.b[k][16 * (wave + NW * cb) + li];
         f4 acc[RB][NCB];
-        fused_layer<OP, NCB, true>(X, ldx, reinterpret_cast<const T *>(p.W[k]), p.ldw[k], k == 0 ? Fk : H, H, wave, lane,
-                             acc);
+        if (k == 0) fused_layer<OP, RB, NCB, NW, NCK0, H / 16, true>(X, ldx, p.W[0], wave, lane, acc);
+        else fused_layer<OP, RB, NCB, NW, H / KC, H / 16, true>(X, ldx, p.W[k], wave, lane, acc);
         __syncthreads();   // every wave has read this layer's input
         const bool last = k + 1 == p.nh;
         float *Zk = p.Z[k];
@@ -556,13 +597,13 @@ __device__ __forceinline__ void mlp_fwd_body(const FusedNN &p, const int64_t m0)
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
-                const int col = 16 * (wave + kFuseWaves * cb) + li;
+                const int col = 16 * (wave + NW * cb) + li;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int rr = 16 * rb + 4 * lg + r;
                     const int64_t row = m0 + rr;
                     const float z = acc[rb][cb][r] * zs + bias[cb];
-                    if (row < p.rows) Zk[row * p.ldz + col] = z;
+                    if (row < p.rows) Zk[row * H + col] = z;
                     const float h = silu_fwd(z);
                     X[rr * ldx + col] = to_op<OP>(h, hin);
                     if (OP != OpType::F32 && last) hf[rr * ldf + col] = h;
@@ -573,19 +614,18 @@ __device__ __forceinline__ void mlp_fwd_body(const FusedNN &p, const int64_t m0)
     // output layer: dout is K (message NNs) or 1 (energy NN)
     const float *hl = (OP == OpType::F32) ? reinterpret_cast<const float *>(X) : hf;
     const int ldl = (OP == OpType::F32) ? ldx : ldf;
-    if (p.dout == K) out_layer<K, float, 64 * NCB, float>(hl, ldl, wo, p.bout, p, m0, tid);
-    else out_layer<1, double, 64 * NCB, double>(hl, ldl, wo64, p.bout64, p, m0, tid);
+    if (p.dout == K) out_layer<K, float, H, NT / BM, float>(hl, ldl, wo, p.bout, p, m0, tid);
+    else out_layer<1, double, H, NT / BM, double>(hl, ldl, wo64, p.bout64, p, m0, tid);
 }
 
 // Output layer of the adjoint: Ga[r][q] = (sum_o G[r][o] Wout[o][q]) * SiLU'(z) for column
-// q = tid % H of rows r0, r0 + 256 / H, ... (z holds those NR = kFuseBM H / 256 rows'
+// q = tid % H of rows r0, r0 + NT / H, ... (z holds those NR = BM H / NT rows'
 // pre-activations); the thread keeps its column of Wout in registers and reads each G row as
 // vectors.  H is a compile-time constant.
-template <OpType OP, int DOUT, int H>
-__device__ inline void out_adjoint(const FusedNN &p, const float *wo, const float *gs,
-                                   const float (&z)[kFuseBM * H / 256], typename Fuse<OP>::T *Ga, int ldh, int64_t m0,
-                                   int tid) {
-    constexpr int NR = kFuseBM * H / 256, rstep = 256 / H;
+template <OpType OP, int DOUT, int H, int BM, int NT>
+__device__ inline void out_adjoint(const FusedNN &p, const float *wo, const float *gs, const float (&z)[BM * H / NT],
+                                   typename Fuse<OP>::T *Ga, int ldh, int64_t m0, int tid) {
+    constexpr int NR = BM * H / NT, rstep = NT / H;
     const int q = tid % H, r0 = tid / H;
     float wq[DOUT];
 #pragma unroll
@@ -610,44 +650,45 @@ __device__ inline void out_adjoint(const FusedNN &p, const float *wo, const floa
 }
 
 // Adjoint of one element's NN: C = dE/dS from G = dE/d(output), using the stored Z_k.
-template <OpType OP, int NCB, int L, int K>
+template <OpType OP, int H, int L, int K, int BM, int NW>
 __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0) {
-    constexpr int NCBF = (L + 1) * K * (K + 1) / 2 > 128 ? 4 : 2;   // column blocks per wave, first layer
     using T = typename Fuse<OP>::T;
-    constexpr int BM = kFuseBM, RB = BM / 16;
+    constexpr int RB = BM / 16, NT = NW * 64, NCB = H / 16 / NW, KC = Fuse<OP>::KC;
+    constexpr int F = fused_features(L, K), NBF = ceil_div(F, 16);
+    constexpr int NCBF = ceil_div(NBF, NW);   // column blocks per wave, first layer
     constexpr int NLK = n_lambda(L) * K, P = K * (K + 1) / 2, NL = n_lambda(L);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
-    const int F = p.F, H = p.H, dout = p.dout;
-    const int ldh = H + Fuse<OP>::PAD, ldr = F + 4;
+    const int dout = p.dout;
+    constexpr int ldh = H + Fuse<OP>::PAD, ldr = F + 4;
     // LDS from `smem` by offset arithmetic only (see the forward kernel).  Region A holds the
     // adjoint tile, updated in place layer by layer, and finally dE/drho; region B holds W_out
     // and the G tile.
-    const int offB = max(BM * ldh * (int)sizeof(T), BM * ldr * 4);
+    constexpr int offB = BM * ldh * (int)sizeof(T) > BM * ldr * 4 ? BM * ldh * (int)sizeof(T) : BM * ldr * 4;
     T *Ga = reinterpret_cast<T *>(smem);
     float *Rb = reinterpret_cast<float *>(smem);          // dE/drho [BM][ldr]
     float *wo = reinterpret_cast<float *>(smem + offB);   // W_out [dout][H]
     float *gs = wo + dout * H;                             // G tile [BM][dout]
     // output layer: zbar[r][q] = (sum_o G[r][o] Wout[o][q]) * SiLU'(Z_{nh-1}[r][q]); thread tid
-    // takes column q = tid % H of rows r0, r0 + 256 / H, ...
+    // takes column q = tid % H of rows r0, r0 + NT / H, ...
     {
-        for (int e = tid; e < dout * H; e += 256) wo[e] = p.Wout[e];
-        for (int e = tid; e < BM * dout; e += 256) {
+        for (int e = tid; e < dout * H; e += NT) wo[e] = p.Wout[e];
+        for (int e = tid; e < BM * dout; e += NT) {
             const int r = e / dout, o = e % dout;
             gs[e] = m0 + r < p.rows ? p.G[(m0 + r) * p.ldg + o] : 0.0f;
         }
-        constexpr int HC = 64 * NCB, NR = BM * HC / 256, rstep = 256 / HC;   // HC = H
-        const int q = tid % HC, r0 = tid / HC;
+        constexpr int NR = BM * H / NT, rstep = NT / H;
+        const int q = tid % H, r0 = tid / H;
         const float *Zl = p.Z[p.nh - 1];
         float z[NR];
 #pragma unroll
         for (int i = 0; i < NR; ++i) {   // rows past the end: as above (out_adjoint zeroes them)
             const int64_t row = min(m0 + r0 + rstep * i, p.rows - 1);
-            z[i] = Zl[row * p.ldz + q];
+            z[i] = Zl[row * H + q];
         }
         __syncthreads();
-        if (dout == K) out_adjoint<OP, K, HC>(p, wo, gs, z, Ga, ldh, m0, tid);
-        else out_adjoint<OP, 1, HC>(p, wo, gs, z, Ga, ldh, m0, tid);
+        if (dout == K) out_adjoint<OP, K, H, BM, NT>(p, wo, gs, z, Ga, ldh, m0, tid);
+        else out_adjoint<OP, 1, H, BM, NT>(p, wo, gs, z, Ga, ldh, m0, tid);
     }
     __syncthreads();
     for (int k = p.nh - 1; k >= 1; --k) {
@@ -661,17 +702,17 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
                 for (int r = 0; r < 4; ++r) {
                     // rows past the end read the last row; their adjoints are set to 0 below
                     const int64_t row = min(m0 + 16 * rb + 4 * lg + r, p.rows - 1);
-                    const int col = 16 * (wave + kFuseWaves * cb) + li;
-                    zp[rb][cb][r] = Zk[row * p.ldz + col];
+                    const int col = 16 * (wave + NW * cb) + li;
+                    zp[rb][cb][r] = Zk[row * H + col];
                 }
         f4 acc[RB][NCB];
-        fused_layer<OP, NCB, false>(Ga, ldh, reinterpret_cast<const T *>(p.W[k]), p.ldw[k], H, H, wave, lane, acc);
+        fused_layer<OP, RB, NCB, NW, H / KC, H / 16, false>(Ga, ldh, p.W[k], wave, lane, acc);
         __syncthreads();   // every wave has read the tile
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
-                const int col = 16 * (wave + kFuseWaves * cb) + li;
+                const int col = 16 * (wave + NW * cb) + li;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int rr = 16 * rb + 4 * lg + r;
@@ -684,13 +725,13 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
     // first layer: dE/drho = zbar_0 W_0 (F columns), into region A once every wave is done
     // reading the adjoint tile
     f4 acc[RB][NCBF];
-    fused_layer<OP, NCBF, false>(Ga, ldh, reinterpret_cast<const T *>(p.W[0]), p.ldw[0], H, F, wave, lane, acc);
+    fused_layer<OP, RB, NCBF, NW, H / KC, NBF, false>(Ga, ldh, p.W[0], wave, lane, acc);
     __syncthreads();
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < NCBF; ++cb) {
-            const int col = 16 * (wave + kFuseWaves * cb) + li;
+            const int col = 16 * (wave + NW * cb) + li;
             if (col >= F) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r) Rb[(16 * rb + 4 * lg + r) * ldr + col] = acc[rb][cb][r];
@@ -698,7 +739,7 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
     __syncthreads();
     // the radial form (L = 0): dE/dS = dE/dx
     if constexpr (L == 0) {
-        for (int it = tid; it < BM * K; it += 256) {
+        for (int it = tid; it < BM * K; it += NT) {
             const int r = it / K, f = it % K;
             if (m0 + r < p.rows) p.C[(m0 + r) * K + f] = Rb[r * ldr + f];
         }
@@ -707,7 +748,7 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
     // density adjoint: dE/dS[lambda][a] = w_lambda sum_b M_l[a][b] S[lambda][b] for lambda of
     // order l, with M_l the symmetric matrix of dE/drho[l] (doubled on the diagonal); one
     // thread per (row, lambda), S read from global
-    for (int it = tid; it < BM * NL; it += 256) {
+    for (int it = tid; it < BM * NL; it += NT) {
         const int r = it / NL, lam = it % NL;
         const int64_t row = m0 + r;
         if (row >= p.rows) continue;
@@ -743,34 +784,27 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
     }
 }
 
-// The kernels: one element's rows (blocks of kFuseBM rows), or several segments of the same NN
-// shape in one launch (block b runs segment s for tile0[s] <= b < tile0[s + 1]).
-template <OpType OP, int NCB, int L, int K>
-__global__ __launch_bounds__(256, 4) void k_mlp_fwd(FusedNN p) {
-    mlp_fwd_body<OP, NCB, L, K>(p, (int64_t)blockIdx.x * kFuseBM);
-}
-template <OpType OP, int NCB, int L, int K>
-__global__ __launch_bounds__(256, 4) void k_mlp_bwd(FusedNN p) {
-    mlp_bwd_body<OP, NCB, L, K>(p, (int64_t)blockIdx.x * kFuseBM);
-}
+// The kernels: segments of the same NN shape (the elements' rows of a layer) in one launch, block b
+// running segment s for tile0[s] <= b < tile0[s + 1].  Two tile shapes (fused_small): 32 rows and
+// 4 waves, four workgroups per CU; and 16 rows, with 8 waves at H = 128, for launches that
+// would leave CUs idle.
 __device__ __forceinline__ int fused_segment(const FusedMulti &pm) {
     int s = 0;
     while (s + 1 < pm.n && (int64_t)blockIdx.x >= pm.tile0[s + 1]) ++s;
     return s;
 }
-template <OpType OP, int NCB, int L, int K>
-__global__ __launch_bounds__(256, 4) void k_mlp_fwd_multi(FusedMulti pm) {
+template <OpType OP, int H, int L, int K, int BM, int NW>
+__global__ __launch_bounds__(NW * 64, BM == 32 ? 4 : 2) void k_mlp_fwd(FusedMulti pm) {
     const int s = fused_segment(pm);
-    mlp_fwd_body<OP, NCB, L, K>(pm.seg[s], ((int64_t)blockIdx.x - pm.tile0[s]) * kFuseBM);
+    mlp_fwd_body<OP, H, L, K, BM, NW>(pm.seg[s], ((int64_t)blockIdx.x - pm.tile0[s]) * BM);
 }
-template <OpType OP, int NCB, int L, int K>
-__global__ __launch_bounds__(256, 4) void k_mlp_bwd_multi(FusedMulti pm) {
+template <OpType OP, int H, int L, int K, int BM, int NW>
+__global__ __launch_bounds__(NW * 64, BM == 32 ? 4 : 2) void k_mlp_bwd(FusedMulti pm) {
     const int s = fused_segment(pm);
-    mlp_bwd_body<OP, NCB, L, K>(pm.seg[s], ((int64_t)blockIdx.x - pm.tile0[s]) * kFuseBM);
+    mlp_bwd_body<OP, H, L, K, BM, NW>(pm.seg[s], ((int64_t)blockIdx.x - pm.tile0[s]) * BM);
 }
 
-bool fused_nn_ok(OpType op, int F, int H, int nh, int dout, int NLK) {
-    (void)op;
+bool fused_nn_ok(int F, int H, int nh, int dout, int NLK) {
     return (H == 64 || H == 128) && F >= 1 && F <= kFuseMaxF && nh >= 1 && nh <= kFuseMaxNh &&
            dout >= 1 && dout <= kFuseMaxOut && NLK >= 1 && NLK <= kFuseMaxNLK;
 }
@@ -826,90 +860,100 @@ void silu_absmax(hipStream_t st, int64_t rows, int H, int ld, const float *Z, fl
     LAUNCH_OK("k_silu_absmax");
 }
 
-static size_t fused_smem(OpType op, bool fwd, int F, int H, int dout, int NLK) {
-    (void)NLK;
+static size_t fused_smem(OpType op, bool fwd, int F, int H, int dout, int BM) {
     const size_t eb = op_bytes(op), pad = op == OpType::F32 ? 4 : (op == OpType::BF16 ? 8 : 16);
-    const size_t Fp = pad_k(F), ldh = H + pad;
+    const size_t ldh = H + pad;
     if (!fwd) {
-        const size_t a = std::max<size_t>(kFuseBM * ldh * eb, (size_t)kFuseBM * (F + 4) * 4);
-        return a + (size_t)(dout * H + kFuseBM * dout) * 4;
+        const size_t a = std::max<size_t>(BM * ldh * eb, (size_t)BM * (F + 4) * 4);
+        return a + (size_t)(dout * H + BM * dout) * 4;
     }
-    const size_t kc = op == OpType::F32 ? 16 : 32, Fk = (F + kc - 1) / kc * kc;
+    const size_t kc = 4 * op_run(op), Fk = (F + kc - 1) / kc * kc;
     const size_t ldx = std::max<size_t>(Fk, H) + pad;
-    size_t b = kFuseBM * ldx * eb;
-    if (op != OpType::F32) b += (size_t)kFuseBM * (H + 4) * 4;
+    size_t b = BM * ldx * eb;
+    if (op != OpType::F32) b += (size_t)BM * (H + 4) * 4;
     return b + (size_t)dout * H * (dout == 1 ? 8 : 4);   // W_out: FP64 for the energy NN
 }
 
-// Launch the fused kernel over nseg segments of the same NN shape: one segment with the
-// per-element kernel, several with the segment-table kernel.
+// Tile shape of a launch.  A 32-row tile alone on a CU takes 19-21 us at H = 128 (FP32): one wave
+// a SIMD waits out every load and barrier, and few rows leave CUs idle.  16-row tiles, with a
+// wave per column block, halve the serial part of a tile and double the tiles, but each reads all
+// the weights and its density part uses a quarter of the lanes.  They are taken while their waves
+// fill the SIMDs at most twice (forward; the adjoint, which has no density prologue,
+// gains longer: 8 times).  us per launch, 32- against 16-row tiles, FP32 Cu shapes:
+//   4,000 atoms   forward 20.8 / 14.5, adjoint 19.6 / 12.3      8,788: 29.9 / 29.7, 29.4 / 23.4
+//   16,384        33.0 / 38.6,         32.3 / 31.1             32,000: 56.8 / 71.0, 62.2 / 59.4
+// BF16 at 8,788: 19.4 / 21.7, 15.6 / 13.0; H = 64 (20,520 water atoms): 14.1 / 14.8, 14.0 / 12.5.
+constexpr int kSimds = 1024;
+static bool fused_small(bool fwd, int H, int64_t tiles16) {
+    const int waves = H == 128 ? 8 : 4;
+    return tiles16 * waves <= (int64_t)(fwd ? 2 : 8) * kSimds;
+}
+
+template <OpType OP, int H, int L, int K, int BM, int NW>
+static void launch_shape(hipStream_t st, bool fwd, unsigned tiles, const FusedMulti &pm) {
+    const FusedNN &p = pm.seg[0];
+    const size_t smem = fused_smem(OP, fwd, p.F, p.H, p.dout, BM);
+    if (fwd) {
+        hipLaunchKernelGGL((k_mlp_fwd<OP, H, L, K, BM, NW>), dim3(tiles), dim3(NW * 64), smem, st, pm);
+    } else if constexpr (OP != OpType::FP8) {
+        hipLaunchKernelGGL((k_mlp_bwd<OP, H, L, K, BM, NW>), dim3(tiles), dim3(NW * 64), smem, st, pm);
+    } else {
+        fail(REANN_E_DEVICE, "mlp_fused: FP8 runs the forward only (its adjoint takes BF16 operands)");
+    }
+}
+
+template <OpType OP, int L, int K>
+static void launch_width(hipStream_t st, bool fwd, bool small, unsigned tiles, const FusedMulti &pm) {
+    if (pm.seg[0].H == 128) {
+        if (small) launch_shape<OP, 128, L, K, kFuseSmallBM, 8>(st, fwd, tiles, pm);
+        else launch_shape<OP, 128, L, K, kFuseBM, 4>(st, fwd, tiles, pm);
+    } else {
+        if (small) launch_shape<OP, 64, L, K, kFuseSmallBM, 4>(st, fwd, tiles, pm);
+        else launch_shape<OP, 64, L, K, kFuseBM, 4>(st, fwd, tiles, pm);
+    }
+}
+
+template <OpType OP>
+static void launch_tiles(hipStream_t st, bool fwd, bool small, unsigned tiles, const FusedMulti &pm) {
+    const int L = pm.seg[0].L, K = pm.seg[0].K;
+    if (L == 2 && K == 8) launch_width<OP, 2, 8>(st, fwd, small, tiles, pm);
+    else if (L == 2 && K == 12) launch_width<OP, 2, 12>(st, fwd, small, tiles, pm);
+    else if (L == 1 && K == 4) launch_width<OP, 1, 4>(st, fwd, small, tiles, pm);
+    else if (L == 2 && K == 4) launch_width<OP, 2, 4>(st, fwd, small, tiles, pm);
+    else if (L == 0 && K == 12) launch_width<OP, 0, 12>(st, fwd, small, tiles, pm);
+    else if (L == 0 && K == 8) launch_width<OP, 0, 8>(st, fwd, small, tiles, pm);
+    else fail(REANN_E_UNSUPPORTED, "mlp_fused: no kernel compiled for this (L, K)");
+}
+
+// Launch the fused kernel over nseg segments of the same NN shape.
 static void launch_fused(hipStream_t st, OpType op, bool fwd, const FusedNN *segs, int nseg) {
     const FusedNN &p = segs[0];
     const int NLK = p.dc.lstart[p.L + 1] * p.K;
-    const int Fwant = p.L == 0 ? p.K : (p.L + 1) * p.K * (p.K + 1) / 2;   // L = 0: the radial form
-    if (!fused_nn_ok(op, p.F, p.H, p.nh, p.dout, NLK) || p.F != Fwant || (p.dout != p.K && p.dout != 1))
+    if (!fused_nn_ok(p.F, p.H, p.nh, p.dout, NLK) || p.F != fused_features(p.L, p.K) ||
+        (p.dout != p.K && p.dout != 1))
         fail(REANN_E_DEVICE, "mlp_fused: unsupported layer shape");
-    FusedMulti pm{};
+    if (nseg > kFuseMaxSeg) fail(REANN_E_DEVICE, "mlp_fused: too many segments");
     int64_t tiles = 0;
-    if (nseg > 1) {
-        if (nseg > kFuseMaxSeg) fail(REANN_E_DEVICE, "mlp_fused: too many segments");
-        pm.n = nseg;
-        for (int s = 0; s < nseg; ++s) {
-            const FusedNN &q = segs[s];
-            if (q.F != p.F || q.H != p.H || q.nh != p.nh || q.dout != p.dout || q.L != p.L || q.K != p.K)
-                fail(REANN_E_DEVICE, "mlp_fused: segments of different shapes");
-            pm.seg[s] = q;
-            pm.tile0[s] = tiles;
-            tiles += (q.rows + kFuseBM - 1) / kFuseBM;
-        }
-        pm.tile0[nseg] = tiles;
-    } else {
-        tiles = (p.rows + kFuseBM - 1) / kFuseBM;
+    for (int s = 0; s < nseg; ++s) tiles += (segs[s].rows + kFuseSmallBM - 1) / kFuseSmallBM;
+    const bool small = fused_small(fwd, p.H, tiles);
+    const int BM = small ? kFuseSmallBM : kFuseBM;
+    FusedMulti pm{};
+    pm.n = nseg;
+    tiles = 0;
+    for (int s = 0; s < nseg; ++s) {
+        const FusedNN &q = segs[s];
+        if (q.F != p.F || q.H != p.H || q.nh != p.nh || q.dout != p.dout || q.L != p.L || q.K != p.K)
+            fail(REANN_E_DEVICE, "mlp_fused: segments of different shapes");
+        pm.seg[s] = q;
+        pm.tile0[s] = tiles;
+        tiles += (q.rows + BM - 1) / BM;
     }
+    pm.tile0[nseg] = tiles;
     if (tiles <= 0) return;
-    const size_t smem = fused_smem(op, fwd, p.F, p.H, p.dout, NLK);
-    const dim3 grid((unsigned)tiles);
-    const bool h128 = p.H == 128;   // the kernels take H = 64 NCB as a compile-time constant
-    const bool multi = nseg > 1;
-#define LK_(OPV, NC, LL, KK)                                                                                  \
-    if (fwd) {                                                                                              \
-        if (multi) hipLaunchKernelGGL((k_mlp_fwd_multi<OPV, NC, LL, KK>), grid, dim3(256), smem, st, pm);   \
-        else hipLaunchKernelGGL((k_mlp_fwd<OPV, NC, LL, KK>), grid, dim3(256), smem, st, p);                \
-    } else {                                                                                                \
-        if (multi) hipLaunchKernelGGL((k_mlp_bwd_multi<OPV, NC, LL, KK>), grid, dim3(256), smem, st, pm);   \
-        else hipLaunchKernelGGL((k_mlp_bwd<OPV, NC, LL, KK>), grid, dim3(256), smem, st, p);                \
-    }
-#define NC_(OPV, LL, KK)                       \
-    if (h128) { LK_(OPV, 2, LL, KK) }          \
-    else { LK_(OPV, 1, LL, KK) }
-#define ALL_(OPV)                                                                       \
-    if (p.L == 2 && p.K == 8) { NC_(OPV, 2, 8) }                                        \
-    else if (p.L == 2 && p.K == 12) { NC_(OPV, 2, 12) }                                 \
-    else if (p.L == 1 && p.K == 4) { NC_(OPV, 1, 4) }                                   \
-    else if (p.L == 2 && p.K == 4) { NC_(OPV, 2, 4) }                                   \
-    else if (p.L == 0 && p.K == 12) { NC_(OPV, 0, 12) }                                 \
-    else if (p.L == 0 && p.K == 8) { NC_(OPV, 0, 8) }                                   \
-    else fail(REANN_E_UNSUPPORTED, "mlp_fused: no kernel compiled for this (L, K)");
-    if (op == OpType::F32) { ALL_(OpType::F32) }
-    else if (op == OpType::BF16) { ALL_(OpType::BF16) }
-    else {
-        if (!fwd) fail(REANN_E_DEVICE, "mlp_fused: FP8 runs the forward only (its adjoint takes BF16 operands)");
-#undef LK_
-#define LK_(OPV, NC, LL, KK)                                                                                  \
-    if (multi) hipLaunchKernelGGL((k_mlp_fwd_multi<OPV, NC, LL, KK>), grid, dim3(256), smem, st, pm);       \
-    else hipLaunchKernelGGL((k_mlp_fwd<OPV, NC, LL, KK>), grid, dim3(256), smem, st, p);
-        ALL_(OpType::FP8)
-#undef LK_
-    }
-#undef ALL_
-#undef NC_
-#undef LK_
+    if (op == OpType::F32) launch_tiles<OpType::F32>(st, fwd, small, (unsigned)tiles, pm);
+    else if (op == OpType::BF16) launch_tiles<OpType::BF16>(st, fwd, small, (unsigned)tiles, pm);
+    else launch_tiles<OpType::FP8>(st, fwd, small, (unsigned)tiles, pm);
     LAUNCH_OK(fwd ? "k_mlp_fwd" : "k_mlp_bwd");
-}
-
-void mlp_fused(hipStream_t st, OpType op, bool fwd, const FusedNN &p) {
-    if (p.rows <= 0) return;
-    launch_fused(st, op, fwd, &p, 1);
 }
 
 int mlp_fused_segments(hipStream_t st, OpType op, bool fwd, const FusedNN *segs, int nseg) {

@@ -28,8 +28,21 @@ void amax_scale(hipStream_t st, const float *A, int64_t rows, int cols, int lda,
 void convert_operand(hipStream_t st, OpType op, const float *src, int rows, int cols, int ld_src, void *dst,
                      int ld_dst, const float *scale);
 
+// Operands of the fused kernels, stored as the fragments their lanes read: for K chunk kc (4 RUN
+// values of k) and block j of 16 rows, lane l holds the RUN values W[16 j + l % 16][4 RUN kc +
+// RUN (l / 16) ..], RUN = 4 (FP32) or 8, at ((kc nblk + j) 64 + l) RUN; zero past the matrix.
+__host__ __device__ constexpr int op_run(OpType op) { return op == OpType::F32 ? 4 : 8; }
+inline size_t packed_elems(OpType op, int rows, int cols) {
+    const int kc = 4 * op_run(op);
+    return (size_t)((rows + 15) / 16 * 16) * (size_t)((cols + kc - 1) / kc * kc);
+}
+// Pack FP32 [rows][cols] (row stride ld_src); for FP8 the values are divided by *scale first.
+void pack_operand(hipStream_t st, OpType op, const float *src, int rows, int cols, int ld_src, void *dst,
+                  const float *scale);
+
 // Fused atomic NN (every layer of one element's NN in one launch, FP32 or BF16 operands).
 constexpr int kFuseBM = 32;      // rows per workgroup
+constexpr int kFuseSmallBM = 16; // rows per workgroup of a launch with few rows
 constexpr int kFuseMaxH = 128;   // hidden width (64 or 128)
 constexpr int kFuseMaxF = 256;   // input width
 constexpr int kFuseMaxNh = 4;    // hidden layers
@@ -42,13 +55,10 @@ struct FusedNN {
     int L, K;                     // angular order and radial channels of the density input
     DensityConsts dc;             // its multinomial weights and component ranges
     const float *S;               // orbital sums [rows][NL*K] (the NN input is their density)
-    // forward: W[k] = layer k as [out][ldw] (gemm_mfma's forward operand)
-    // adjoint: W[k] = layer k transposed, [in][ldw]
+    // packed operands (pack_operand): forward, layer k [out][in]; adjoint, its transpose
     const void *W[kFuseMaxNh];
-    int ldw[kFuseMaxNh];
     const float *b[kFuseMaxNh];   // forward: hidden-layer biases
-    float *Z[kFuseMaxNh];         // pre-activations [rows][ldz]: written by forward, read by adjoint
-    int ldz;
+    float *Z[kFuseMaxNh];         // pre-activations [rows][H]: written by forward, read by adjoint
     const float *Wout, *bout;     // output layer [dout][H], [dout] (FP32)
     const double *Wout64, *bout64;   // forward with dout = 1 (the energy NN): the same in FP64
     // FP8 forward only (1 / 1 / NULL otherwise): layer k's product is multiplied by zscale[k]
@@ -76,7 +86,7 @@ static_assert(sizeof(FusedMulti) < 3072, "kernel arguments");
 
 // Whether the fused kernels take these shapes (every operand type: FP8 runs the forward only,
 // its adjoint takes BF16 operands).
-bool fused_nn_ok(OpType op, int F, int H, int nh, int dout, int NLK);
+bool fused_nn_ok(int F, int H, int nh, int dout, int NLK);
 
 // FP8 calibration from FP32 activations: out[f] = max over the rows of |rho_f| of the density of
 // S [rows][NL*K] (f = (l, a <= b) in the feature order); out[F] must be zero on entry.
@@ -85,9 +95,8 @@ void density_absmax(hipStream_t st, int L, int K, int64_t rows, const DensityCon
 void silu_absmax(hipStream_t st, int64_t rows, int H, int ld, const float *Z, float *out);
 // Forward (fwd = true: density of S, hidden layers, Z stores, output layer with FP64
 // accumulation) or adjoint (fwd = false: output layer, hidden layers, first layer, density
-// adjoint to dE/dS) of one element's NN.
-void mlp_fused(hipStream_t st, OpType op, bool fwd, const FusedNN &p);
-// The same over nseg segments of one NN shape, kFuseMaxSeg to a launch; returns the launches.
+// adjoint to dE/dS) over nseg segments of one NN shape, kFuseMaxSeg to a launch; returns the
+// launches.
 int mlp_fused_segments(hipStream_t st, OpType op, bool fwd, const FusedNN *segs, int nseg);
 
 inline size_t op_bytes(OpType op) { return op == OpType::F32 ? 4 : (op == OpType::BF16 ? 2 : 1); }

@@ -107,12 +107,23 @@ const MfmaSet &Model::mfma(int device, hipStream_t st, bool energy, OpType op) {
     if (!host.empty()) HIP_OK(hipMemcpyAsync(tmp.p, host.data(), host.size() * 4, hipMemcpyHostToDevice, st));
     set->scales.ensure(std::max<size_t>(scales.size(), 1) * 4);
     if (!scales.empty()) HIP_OK(hipMemcpyAsync(set->scales.p, scales.data(), scales.size() * 4, hipMemcpyHostToDevice, st));
+    // the fused kernels' operands are packed fragments, the per-layer kernel's are padded rows
+    const bool packed = fused_form();
     const size_t eb = op_bytes(op);
-    set->buf.ensure(std::max<size_t>(host.size(), 1) * eb);
+    std::vector<size_t> ooff(foff.size() + 1, 0);
     for (size_t i = 0; i < foff.size(); ++i) {
-        const size_t ob = foff[i] * eb;
-        convert_operand(st, op, tmp.as<float>() + foff[i], rows_[i], cols_[i], lds_[i], set->buf.as<char>() + ob,
-                        lds_[i], set->scales.as<float>() + i);
+        const size_t ne = packed ? packed_elems(op, rows_[i], cols_[i]) : (size_t)rows_[i] * lds_[i];
+        ooff[i + 1] = ooff[i] + (ne * eb + 15) / 16 * 16;
+    }
+    set->buf.ensure(std::max<size_t>(ooff.back(), 1));
+    for (size_t i = 0; i < foff.size(); ++i) {
+        const size_t ob = ooff[i];
+        if (packed)
+            pack_operand(st, op, tmp.as<float>() + foff[i], rows_[i], cols_[i], lds_[i], set->buf.as<char>() + ob,
+                         set->scales.as<float>() + i);
+        else
+            convert_operand(st, op, tmp.as<float>() + foff[i], rows_[i], cols_[i], lds_[i], set->buf.as<char>() + ob,
+                            lds_[i], set->scales.as<float>() + i);
         if (i % 2 == 0) set->off_fwd.push_back(ob);
         else set->off_bwd.push_back(ob);
     }
@@ -277,11 +288,12 @@ int64_t Plan::collect_timing(double *ms, int64_t *nlaunch) {
     return steps;
 }
 
-// whether both atomic NNs run as fused kernels (FP32 or BF16 operands, supported widths)
-bool Plan::fused() const {
+// whether both atomic NNs run as fused kernels (FP32, BF16 or FP8 operands)
+bool Plan::fused() const { return !fp64 && m->fused_form(); }
+
+bool Model::fused_form() const {
     // the fused kernels form the paired density (or, at L = 0, take the radial form's sums)
-    return !fp64 && m->form != REANN_FORM_DIAG && fused_nn_ok(op, m->F, m->H, m->nh, m->K, m->NL * m->K) &&
-           fused_nn_ok(op, m->F, m->H, m->nh, 1, m->NL * m->K);
+    return form != REANN_FORM_DIAG && fused_nn_ok(F, H, nh, K, NL * K) && fused_nn_ok(F, H, nh, 1, NL * K);
 }
 
 void Plan::alloc_buffers() {
@@ -389,14 +401,12 @@ int Plan::nn_forward(hipStream_t st, int t, bool energy) {
             for (int k = 0; k < nh; ++k) {
                 const size_t qi = (size_t)nn_index * nh + k;
                 f.W[k] = mf->buf.as<char>() + mf->off_fwd[qi];
-                f.ldw[k] = mf->ld_fwd[qi];
                 f.b[k] = (const float *)(p + lay.b_off[k] * rs);
                 f.Z[k] = (float *)(Zptr(t, k) + (size_t)a * H * rs);
                 f.zscale[k] = f8 ? fp8_zscale[energy ? 1 : 0][qi] : 1.0f;
                 f.hinv[k] = f8 ? fp8_hinv[energy ? 1 : 0][qi] : 1.0f;
             }
             f.xinv = f8 ? fp8_xinv[energy ? 1 : 0].as<float>() + (size_t)nn_index * F : nullptr;
-            f.ldz = H;
             f.Wout = (const float *)(p + lay.w_off[nh] * rs);
             f.bout = (const float *)(p + lay.b_off[nh] * rs);
             if (energy) {   // the energy readout takes its weights and bias in FP64
@@ -478,10 +488,8 @@ int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg) 
             for (int k = 0; k < nh; ++k) {
                 const size_t qi = (size_t)nn_index * nh + k;
                 f.W[k] = mf->buf.as<char>() + mf->off_bwd[qi];
-                f.ldw[k] = mf->ld_bwd[qi];
                 f.Z[k] = (float *)(Zptr(t, k) + (size_t)a * H * rs);
             }
-            f.ldz = H;
             f.Wout = (const float *)(p + lay.w_off[nh] * rs);
             f.G = (const float *)gin; f.ldg = ldin;
             f.C = (float *)(Sbar.as<char>() + (size_t)a * m->NL * m->K * rs); f.ldc = m->NL * m->K;
@@ -620,11 +628,15 @@ void Plan::calibrate_fp8(const double *d_pos, hipStream_t st) {
         set->scales.ensure(std::max<size_t>(scales.size(), 1) * 4);
         if (!scales.empty())
             HIP_OK(hipMemcpyAsync(set->scales.p, scales.data(), scales.size() * 4, hipMemcpyHostToDevice, st));
-        set->buf.ensure(std::max<size_t>(host.size(), 1));
+        size_t bytes = 0;   // one byte per element
         for (size_t i = 0; i < foff.size(); ++i) {
-            convert_operand(st, OpType::FP8, tmp.as<float>() + foff[i], rows_[i], cols_[i], lds_[i],
-                            set->buf.as<char>() + foff[i], lds_[i], set->scales.as<float>() + i);
-            set->off_fwd[i] = foff[i];   // one byte per element: the byte offset equals the float offset
+            set->off_fwd[i] = bytes;
+            bytes += (packed_elems(OpType::FP8, rows_[i], cols_[i]) + 15) / 16 * 16;
+        }
+        set->buf.ensure(std::max<size_t>(bytes, 1));
+        for (size_t i = 0; i < foff.size(); ++i) {
+            pack_operand(st, OpType::FP8, tmp.as<float>() + foff[i], rows_[i], cols_[i], lds_[i],
+                         set->buf.as<char>() + set->off_fwd[i], set->scales.as<float>() + i);
         }
         float *dx = static_cast<float *>(fp8_xinv[e].ensure(xinv.size() * 4));
         HIP_OK(hipMemcpyAsync(dx, xinv.data(), xinv.size() * 4, hipMemcpyHostToDevice, st));

@@ -27,8 +27,8 @@ struct NNLayout {
 NNLayout nn_layout(int F, int H, int nh, int out);
 
 // Matrix-core operands of the hidden layers of every atomic NN: for NN q and hidden layer k,
-// the forward operand W_k [dout][pad(din)] and the backward operand W_k^T [din][pad(dout)],
-// in one operand type, with one scale per matrix (FP8: amax/448; otherwise 1).
+// the forward operand W_k and the backward operand W_k^T, packed (pack_operand) or for the
+// per-layer kernel as rows [dout][pad(din)] and [din][pad(dout)], in one operand type, with one scale per matrix (FP8: amax/448; otherwise 1).
 struct MfmaSet {
     DevBuf buf, scales;
     std::vector<size_t> off_fwd, off_bwd;   // bytes, index q * nh + k
@@ -62,6 +62,8 @@ struct Model {
     DeviceWeights &weights(int device, hipStream_t st);
     // matrix-core operands of the message (energy = false) or energy NNs for `op`
     const MfmaSet &mfma(int device, hipStream_t st, bool energy, OpType op);
+    // whether the atomic NNs run on the fused kernels (their operands are then packed)
+    bool fused_form() const;
     // whether the device copies an evaluation at `prec` reads already exist on `device`
     bool on_device(int device, int prec);
     EdgeConsts edge_consts() const;
