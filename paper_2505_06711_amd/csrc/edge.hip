@@ -158,15 +158,22 @@ __global__ void k_compact(EdgeArgs a, double rc2, int32_t *__restrict__ col2, in
     }
 }
 
-// Forward edge pass: the 4 lanes of a quad own one row, lane q the channels
+// Forward edge pass: a quad of 4 lanes takes edges of one row, lane q the channels
 // m = q K/4 .. (q+1) K/4 - 1 (a contiguous block, so a neighbour's message block is one
 // vector load and the lane's part of S is written with vector stores).
 // The row's edges are taken in groups of 4: lane q evaluates the geometry of edge 4g + q
 // (r, f_c and the angular terms, from one position gather), and the quad exchanges these
 // with DPP quad broadcasts, so that every lane accumulates all 4 edges into its channels.
-// The list entries, positions and messages of group g + 1 are loaded while group g is
+// The list entries, positions and messages of the quad's next group are loaded while one is
 // evaluated (indices clamped to the row's last edge; a lane past the end contributes 0).
+// QPR quads share a row (quad a takes groups a, a + QPR, ...) and add their sums at the end: with
+// few rows a row's 13-20 groups in series are what a launch waits for, and with many the shorter
+// loops still help until the padding of a row's last round of groups costs more (a row of 53
+// edges: 56 slots in one quad, 64 in four).  us per launch, 1 / 4 quads: 192 water atoms 14.7 / 6.0,
+// 20,520 24.3 / 17.8, 192,000 115.8 / 111.4, 1.2M 661 / 684; Cu 4,000 atoms 23.0 / 8.1, 100,800
+// 103.5 / 93.3; FP64 Cu 6,864 37.8 / 19.8.
 constexpr int kFwdLanes = 4;
+constexpr int64_t kFwdQuadRows = 400000;   // rows up to which 4 quads share one
 
 // DPP lane moves within rows of 16 lanes.  The controls used here make every lane read an
 // active lane of its own row, so no lane keeps an old value (and none reads an out-of-range
@@ -182,20 +189,21 @@ constexpr int kDppQuadXor1 = 0xB1;      // quad_perm [1, 0, 3, 2]
 constexpr int kDppQuadXor2 = 0x4E;      // quad_perm [2, 3, 0, 1]
 constexpr int kDppRowHalfMirror = 0x141;   // lane i <- lane 7 - i within each group of 8
 constexpr int kDppRowMirror = 0x140;       // lane i <- lane 15 - i within each row of 16
+constexpr int kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;   // lane i <- lane (i - 4, i - 8) mod 16
 
 // value of lane SRC of this lane's quad (all 4 lanes must be active)
 template <int SRC, typename V> __device__ inline V quad_bcast(V v) { return dpp_move<SRC * 0x55>(v); }
 
-template <int L, int K, typename R>
+template <int L, int K, typename R, int QPR>
 __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeConsts ec, const R *__restrict__ c,
                                                   R *__restrict__ S) {
     constexpr int NL = n_lambda(L);
     constexpr int G = kFwdLanes, KG = K / G;
     static_assert(K % G == 0, "K must be a multiple of the lanes per row");
     const int64_t t = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    const int64_t i = t / G;
-    const int q = (int)(t % G);
-    if (i >= a.n) return;   // the whole quad leaves together
+    const int64_t i = t / (G * QPR);
+    const int q = (int)(t % G), quad = (int)(t / G % QPR);
+    if (i >= a.n) return;   // the whole row leaves together
     R acc[NL][KG];
 #pragma unroll
     for (int l = 0; l < NL; ++l)
@@ -211,13 +219,13 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
     const int64_t lo = cl.row[i], gb = cl.row[i + 1] - cl.ngh[i];
     auto slot = [&](int e) -> int64_t { return e < nl ? lo + e : gb + (e - nl); };
     const int ngroups = (cnt + G - 1) / G;
-    // group 0 in registers, and the own list entry of group 1
+    // the quad's first group in registers, and the own list entry of its second
     double xo = 0.0, yo = 0.0, zo = 0.0;
     R cg[G][KG];
     int32_t jnext = 0;
     if (ngroups > 0) {
-        const int32_t j0 = cl.col[slot(min(q, last))];
-        jnext = cl.col[slot(min(G + q, last))];
+        const int32_t j0 = cl.col[slot(min(quad * G + q, last))];
+        jnext = cl.col[slot(min((quad + QPR) * G + q, last))];
         { const double4 q = a.p4[j0]; xo = q.x; yo = q.y; zo = q.z; }
         const int32_t js[G] = {quad_bcast<0>(j0), quad_bcast<1>(j0), quad_bcast<2>(j0), quad_bcast<3>(j0)};
 #pragma unroll
@@ -225,7 +233,7 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
 #pragma unroll
             for (int u = 0; u < KG; ++u) cg[sl][u] = c[(int64_t)js[sl] * K + KG * q + u];
     }
-    for (int g = 0; g < ngroups; ++g) {
+    for (int g = quad; g < ngroups; g += QPR) {
         const double dx = xo - xi, dy = yo - yi, dz = zo - zi;
         const bool live = g * G + q <= last;
         R cur[G][KG];
@@ -233,7 +241,7 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
         for (int sl = 0; sl < G; ++sl)
 #pragma unroll
             for (int u = 0; u < KG; ++u) cur[sl][u] = cg[sl][u];
-        {   // group g + 1: own position, the quad's messages, and the own entry of group g + 2
+        {   // the next group: own position, the quad's messages, and the own entry of the one after
             const int32_t j1 = jnext;
             { const double4 q = a.p4[j1]; xo = q.x; yo = q.y; zo = q.z; }
             const int32_t js[G] = {quad_bcast<0>(j1), quad_bcast<1>(j1), quad_bcast<2>(j1), quad_bcast<3>(j1)};
@@ -241,7 +249,7 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
             for (int sl = 0; sl < G; ++sl)
 #pragma unroll
                 for (int u = 0; u < KG; ++u) cg[sl][u] = c[(int64_t)js[sl] * K + KG * q + u];
-            jnext = cl.col[slot(min((g + 2) * G + q, last))];
+            jnext = cl.col[slot(min((g + 2 * QPR) * G + q, last))];
         }
         // own edge: geometry
         const double d2 = dx * dx + dy * dy + dz * dz;
@@ -272,11 +280,23 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
         REANN_FWD_SRC(3)
 #undef REANN_FWD_SRC
     }
+    static_assert(QPR == 1 || QPR == 4, "a row is one quad or one DPP row of 4");
     R *out = S + i * NL * K + KG * q;
+    if constexpr (QPR == 4) {   // the 4 quads' sums (the same value in each), then a share of the stores
+#pragma unroll
+        for (int l = 0; l < NL; ++l)
+#pragma unroll
+            for (int u = 0; u < KG; ++u) {
+                acc[l][u] += dpp_move<kDppRowRor8>(acc[l][u]);
+                acc[l][u] += dpp_move<kDppRowRor4>(acc[l][u]);
+            }
+    }
 #pragma unroll
     for (int l = 0; l < NL; ++l)
+        if (l % QPR == quad) {
 #pragma unroll
-        for (int u = 0; u < KG; ++u) out[l * K + u] = acc[l][u];
+            for (int u = 0; u < KG; ++u) out[l * K + u] = acc[l][u];
+        }
 }
 
 // Per-edge radial/cutoff factors shared by both adjoint roles.
@@ -328,38 +348,45 @@ constexpr int kRowsPerBlock = 8;   // 256 threads = 8 half-waves, one row each
 // adds +g to F_k and the symmetric part of -d (x) g to the virial; the edge's record gets g
 // and (CBAR) the terms
 //   f_c R_m sum_lambda Sbar_k[lambda][m] A_lambda(d)  of  cbar_j[m].
-// kCentreLanes lanes share a row and take its edges in turn; Sbar_k is staged in LDS and
+// LPR lanes share a row and take its edges in turn; Sbar_k is staged in LDS and
 // read by all of them.  Each lane runs a two-stage pipeline: the list entry of its edge after
 // next and the position and message of its next edge are loaded while the current edge is
 // evaluated.  The record of edge k -> j is stored at the edge's compacted slot f (so a row's
 // records are contiguous): rec[f * RS + 0..2] = g, rec[f * RS + 4 + m] = terms (RS = 4 + K
 // with CBAR, 4 without).
-constexpr int kCentreLanes = 16;
-constexpr int kCentreRows = 256 / kCentreLanes;
+// 16 lanes leave about 5 edges in series per lane and waste few slots; a launch of few rows does
+// not fill the chip with them and waits for that series, so it takes more lanes per row.  us per
+// launch with message terms, 16 / 32 / 64 lanes: 192 water atoms 9.4 / 7.7 / 5.8, 1,372 Cu atoms 16.8 /
+// 12.8 / 11.2, 4,000 18.9 / 16.5 / 19.4, 8,232 water atoms 15.8 / 16.2 / 17.8, 20,520 28.3 / 30.6 / 37.4
+// (FP64: 256 Cu atoms 22.5 / 16.1 / 12.9, 3,000 water atoms 15.6 / 14.9 / 15.4, 6,864 Cu 51 / 63 / 80).
+static int centre_lanes(int64_t n) { return n <= 1536 ? 64 : (n <= 4096 ? 32 : 16); }
 
-// Sum over the kCentreLanes = 16 lanes of a row (one DPP row, all lanes active): the quad
-// sums, then each lane adds the mirrored lane's value within its group of 8 (the other quad)
-// and within the row (the other half), so every lane ends with the row's total.
-static_assert(kCentreLanes == 16, "row sums are formed within a DPP row of 16 lanes");
-template <typename R> __device__ inline R row_sum(R v) {
+// Sum over the LPR lanes of a row (all active): the quad sums, then each lane adds the mirrored
+// lane's value within its group of 8 (the other quad) and within its DPP row of 16 (the other
+// half), and for wider rows the other DPP rows', so every lane ends with the row's total.
+template <int LPR, typename R> __device__ inline R row_sum(R v) {
+    static_assert(LPR == 16 || LPR == 32 || LPR == 64, "lanes per row");
     v += dpp_move<kDppQuadXor1>(v);
     v += dpp_move<kDppQuadXor2>(v);
     v += dpp_move<kDppRowHalfMirror>(v);
-    return v + dpp_move<kDppRowMirror>(v);
+    v += dpp_move<kDppRowMirror>(v);
+    if constexpr (LPR >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (LPR == 64) v += __shfl_xor(v, 32, 64);
+    return v;
 }
 
-template <int L, int K, typename R, bool CBAR>
+template <int L, int K, typename R, bool CBAR, int LPR>
 __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(EdgeArgs a, CutList cl, EdgeConsts ec, const R *__restrict__ c,
                                                     const R *__restrict__ Sbar, R *__restrict__ F,
                                                     double *__restrict__ Wpart, R *__restrict__ rec) {
-    constexpr int NL = n_lambda(L), LPR = kCentreLanes;
+    constexpr int NL = n_lambda(L), kCentreRows = 256 / LPR;
     constexpr int RS = CBAR ? 4 + K : 4;
     constexpr LamTab<L> LT{};
     __shared__ R sS[kCentreRows][NL * K];
     __shared__ double sW[kCentreRows][9];
     const int grp = threadIdx.x / LPR, lane = threadIdx.x % LPR;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t row0 = tile * kCentreRows;
+    const int64_t row0 = tile * kCentreRows;   // one row per LPR lanes
     for (int t = threadIdx.x; t < kCentreRows * NL * K; t += 256) {
         const int64_t rr = row0 + t / (NL * K);
         sS[t / (NL * K)][t % (NL * K)] = rr < a.n ? Sbar[row0 * NL * K + t] : R(0);
@@ -473,10 +500,10 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
             W[5] -= R(0.5) * (ddy * gz + ddz * gy);
         }
     }
-    f0 = row_sum(f0); f1 = row_sum(f1); f2 = row_sum(f2);
+    f0 = row_sum<LPR>(f0); f1 = row_sum<LPR>(f1); f2 = row_sum<LPR>(f2);
     double Wd[6];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) Wd[q] = row_sum(double(W[q]));
+    for (int q = 0; q < 6; ++q) Wd[q] = row_sum<LPR>(double(W[q]));
     if (lane == 0) {
         if (x < a.n) { F[3 * x] += f0; F[3 * x + 1] += f1; F[3 * x + 2] += f2; }
         sW[grp][0] = Wd[0]; sW[grp][4] = Wd[1]; sW[grp][8] = Wd[2];
@@ -584,28 +611,39 @@ void compact_cutoff(hipStream_t st, const EdgeArgs &a, double r_c, CutList &cl) 
 void edge_forward(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl, const EdgeConsts &ec,
                   const void *c, void *S) {
     const int B = 256;
-    const int64_t nt = a.n * kFwdLanes;
-#define FWD(LL, KK)                                                                                       \
-    if (fp64)                                                                                             \
-        hipLaunchKernelGGL((k_edge_fwd<LL, KK, double>), dim3(grid_for(nt, B)), dim3(B), 0, st, a, cl, ec, \
-                           (const double *)c, (double *)S);                                               \
-    else                                                                                                  \
-        hipLaunchKernelGGL((k_edge_fwd<LL, KK, float>), dim3(grid_for(nt, B)), dim3(B), 0, st, a, cl, ec,  \
-                           (const float *)c, (float *)S);
+    const bool few = a.n <= kFwdQuadRows;
+    const int64_t nt = a.n * kFwdLanes * (few ? 4 : 1);
+#define FWD_T(LL, KK, R, QQ)                                                                                \
+    hipLaunchKernelGGL((k_edge_fwd<LL, KK, R, QQ>), dim3(grid_for(nt, B)), dim3(B), 0, st, a, cl, ec,      \
+                       (const R *)c, (R *)S);
+#define FWD(LL, KK)                                         \
+    if (fp64) {                                             \
+        if (few) { FWD_T(LL, KK, double, 4) }               \
+        else { FWD_T(LL, KK, double, 1) }                   \
+    } else {                                                \
+        if (few) { FWD_T(LL, KK, float, 4) }                \
+        else { FWD_T(LL, KK, float, 1) }                    \
+    }
     REANN_LK_DISPATCH(L, K, FWD);
 #undef FWD
+#undef FWD_T
     LAUNCH_OK("k_edge_fwd");
 }
 
-int edge_backward_blocks(int64_t n_ext) { return grid_for(n_ext, kCentreRows); }
+int edge_backward_blocks(int64_t n) { return grid_for(n, 256 / centre_lanes(n)); }
 
 int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
                         const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, void *F, double *Wpart,
                         void *rec) {
-    const int nbc = grid_for(a.n, kCentreRows);
-#define CEN_T(LL, KK, R, CB)                                                                                       \
-    hipLaunchKernelGGL((k_adj_centre<LL, KK, R, CB>), dim3(nbc), dim3(256), 0, st, a, cl, ec, (const R *)c,      \
+    const int nbc = edge_backward_blocks(a.n);
+    const int lanes = centre_lanes(a.n);
+#define CEN_L(LL, KK, R, CB, LP)                                                                                  \
+    hipLaunchKernelGGL((k_adj_centre<LL, KK, R, CB, LP>), dim3(nbc), dim3(256), 0, st, a, cl, ec, (const R *)c, \
                        (const R *)Sbar, (R *)F, Wpart, (R *)rec);
+#define CEN_T(LL, KK, R, CB)                                    \
+    if (lanes == 64) { CEN_L(LL, KK, R, CB, 64) }               \
+    else if (lanes == 32) { CEN_L(LL, KK, R, CB, 32) }          \
+    else { CEN_L(LL, KK, R, CB, 16) }
 #define CEN(LL, KK)                                             \
     if (fp64) {                                                 \
         if (want_cbar) { CEN_T(LL, KK, double, true) }          \
@@ -617,6 +655,7 @@ int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs 
     REANN_LK_DISPATCH(L, K, CEN);
 #undef CEN
 #undef CEN_T
+#undef CEN_L
     LAUNCH_OK("k_adj_centre");
     return nbc;
 }

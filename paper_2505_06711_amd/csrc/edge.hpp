@@ -59,7 +59,7 @@ void edge_adjoint_gather(hipStream_t st, bool fp64, int K, const EdgeArgs &a, co
                          bool make_rslot, const void *rec, void *F, void *cbar);
 // Values per edge record: the edge gradient (3, padded to 4) and K adjoint-message terms.
 inline int edge_record_elems(int K) { return 4 + K; }
-int edge_backward_blocks(int64_t n_ext);
+int edge_backward_blocks(int64_t n);   // blocks of the centre-role launch over n local rows
 
 // c[n + g][:] = c[owner[g]][:]
 void ghost_gather(hipStream_t st, bool fp64, int64_t n, int64_t n_gh, int K, const int32_t *owner, void *c);

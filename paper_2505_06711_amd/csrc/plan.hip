@@ -320,7 +320,7 @@ void Plan::alloc_buffers() {
     }
     cbar.ensure((size_t)ne * K * rs);
     this->F.ensure((size_t)ne * 3 * rs);
-    Wpart.ensure((size_t)T * (edge_backward_blocks(ne) + 1) * 9 * 8);   // per layer, summed once
+    Wpart.ensure((size_t)T * (edge_backward_blocks(n) + 1) * 9 * 8);   // per layer, summed once
     disp.ensure(1025 * 8);
     col2.ensure((size_t)(nl.n_pairs + 1) * 4);
     fslot.ensure((size_t)(nl.n_pairs + 1) * 4);

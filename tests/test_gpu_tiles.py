@@ -1,5 +1,6 @@
-"""The fused NN kernels' two tile shapes: row counts at the edges of a 16- and a 32-row tile, a single
-row, and both sides of the rule that chooses between the shapes, in FP32 and BF16.
+"""Row counts where the launches of the evaluation change shape, in FP32 and BF16: the fused NN kernels'
+16- and 32-row tiles (edges of a tile, a single row, both sides of the rule between them) and the
+lanes that share a row in the edge adjoint (64, 32 or 16).
 
 FP32 within the FP32 path's bounds (1e-6 energy, 1e-5 of the force RMS and of max|F|) against the
 FP64 oracle; BF16 as a layout check (1% energy and 2% force RMSE per hidden layer and MP layer: the
@@ -34,8 +35,8 @@ def crystal(n, seed):
 
 
 # rows: one; tile edges of 16 and 32; forward rule at 256 tiles of 16 rows (H = 128) and 512 (H = 64);
-# adjoint rule at 1,024 (H = 128) and 2,048 (H = 64)
-@pytest.mark.parametrize("hidden,n", [(128, 1), (128, 15), (128, 17), (128, 33), (128, 4096), (128, 4097), (128, 16384),
+# adjoint rule at 1,024 (H = 128) and 2,048 (H = 64); edge adjoint at 1,536 and 4,096 rows
+@pytest.mark.parametrize("hidden,n", [(128, 1), (128, 15), (128, 17), (128, 33), (128, 1536), (128, 1537), (128, 4096), (128, 4097), (128, 16384),
                                       (128, 16385), (64, 31), (64, 8192), (64, 8193), (64, 32768), (64, 32769)])
 @pytest.mark.parametrize("prec", ["fp32", "bf16"])
 def test_row_counts(rn, ctx, oracle_lib, hidden, n, prec):
