@@ -101,7 +101,12 @@ __device__ inline void angular(R ux, R uy, R uz, R s, R *A, R (*dA)[3]) {
 constexpr int kCompactPasses = 8;   // passes of 16 entries whose loads are issued together
 
 __global__ void k_compact(EdgeArgs a, double rc2, int32_t *__restrict__ col2, int32_t *__restrict__ fslot,
-                          int32_t *__restrict__ cpos, int32_t *__restrict__ nloc, int32_t *__restrict__ ngh) {
+                          int32_t *__restrict__ cpos, int32_t *__restrict__ nloc, int32_t *__restrict__ ngh,
+                          unsigned long long *__restrict__ disp, double *__restrict__ host_disp) {
+    if (disp && blockIdx.x == 0 && threadIdx.x == 0) {   // the refresh's displacement maximum, for the host
+        *host_disp = __longlong_as_double((long long)*disp);
+        *disp = 0ull;
+    }
     // 16 lanes per row take the row's entries 16 at a time (a pass); a ballot gives each
     // in-cutoff entry its rank, so the packed order equals a sequential scan of the row.  The
     // entries of up to kCompactPasses passes are loaded at once, then their neighbours'
@@ -378,7 +383,7 @@ template <int LPR, typename R> __device__ inline R row_sum(R v) {
 template <int L, int K, typename R, bool CBAR, int LPR>
 __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(EdgeArgs a, CutList cl, EdgeConsts ec, const R *__restrict__ c,
                                                     const R *__restrict__ Sbar, R *__restrict__ F,
-                                                    double *__restrict__ Wpart, R *__restrict__ rec) {
+                                                    double *__restrict__ Wpart, R *__restrict__ rec, int first) {
     constexpr int NL = n_lambda(L), kCentreRows = 256 / LPR;
     constexpr int RS = CBAR ? 4 + K : 4;
     constexpr LamTab<L> LT{};
@@ -505,7 +510,11 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
 #pragma unroll
     for (int q = 0; q < 6; ++q) Wd[q] = row_sum<LPR>(double(W[q]));
     if (lane == 0) {
-        if (x < a.n) { F[3 * x] += f0; F[3 * x + 1] += f1; F[3 * x + 2] += f2; }
+        if (x < a.n) {
+            F[3 * x] = first ? f0 : F[3 * x] + f0;
+            F[3 * x + 1] = first ? f1 : F[3 * x + 1] + f1;
+            F[3 * x + 2] = first ? f2 : F[3 * x + 2] + f2;
+        }
         sW[grp][0] = Wd[0]; sW[grp][4] = Wd[1]; sW[grp][8] = Wd[2];
         sW[grp][1] = sW[grp][3] = Wd[3];
         sW[grp][2] = sW[grp][6] = Wd[4];
@@ -524,7 +533,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
 // F_k -= sum g and, with CBAR, cbar_k[m] = sum of the terms.  The reverse of an in-cutoff
 // entry is in cutoff (its displacement is the exact negation), so its compacted slot is set.
 // MAKE (the step's first gather) finds that slot through fslot, rev and cpos and stores it in
-// rslot; the later gathers read rslot.  With CBAR 4 lanes share an edge record (one group
+// rslot, and sets the ghosts' F (nothing has written it yet); the later gathers read rslot.  With CBAR 4 lanes share an edge record (one group
 // of 4 values each, 8 edges per pass of the half-wave); without it a lane takes an edge.
 template <int K, typename R, bool CBAR, bool MAKE>
 __global__ __launch_bounds__(256) void k_adj_gather(EdgeArgs a, CutList cl, const R *__restrict__ rec,
@@ -582,7 +591,8 @@ __global__ __launch_bounds__(256) void k_adj_gather(EdgeArgs a, CutList cl, cons
         for (int q = 0; q < 4; ++q) acc[q] += __shfl_xor(acc[q], o, 32);
     if (eg == 0) {
         if (part == 0) {
-            F[3 * x] -= acc[0]; F[3 * x + 1] -= acc[1]; F[3 * x + 2] -= acc[2];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) F[3 * x + q] = (MAKE && x >= a.n ? R(0) : F[3 * x + q]) - acc[q];
         } else if (CBAR && part < NP) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) cbar[x * K + 4 * (part - 1) + q] = acc[q];
@@ -601,9 +611,10 @@ __global__ __launch_bounds__(256) void k_adj_gather(EdgeArgs a, CutList cl, cons
         else fail(REANN_E_UNSUPPORTED, "no edge kernel compiled for this (L, K)"); \
     } while (0)
 
-void compact_cutoff(hipStream_t st, const EdgeArgs &a, double r_c, CutList &cl) {
+void compact_cutoff(hipStream_t st, const EdgeArgs &a, double r_c, CutList &cl, unsigned long long *disp,
+                    double *host_disp) {
     hipLaunchKernelGGL(k_compact, dim3(grid_for(a.n_ext * 16, 256)), dim3(256), 0, st, a, r_c * r_c, cl.col, cl.fslot,
-                       cl.cpos, cl.nloc, cl.ngh);
+                       cl.cpos, cl.nloc, cl.ngh, disp, host_disp);
     LAUNCH_OK("k_compact");
 }
 
@@ -633,13 +644,13 @@ void edge_forward(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, co
 int edge_backward_blocks(int64_t n) { return grid_for(n, 256 / centre_lanes(n)); }
 
 int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
-                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, void *F, double *Wpart,
-                        void *rec) {
+                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, bool first, void *F,
+                        double *Wpart, void *rec) {
     const int nbc = edge_backward_blocks(a.n);
     const int lanes = centre_lanes(a.n);
 #define CEN_L(LL, KK, R, CB, LP)                                                                                  \
     hipLaunchKernelGGL((k_adj_centre<LL, KK, R, CB, LP>), dim3(nbc), dim3(256), 0, st, a, cl, ec, (const R *)c, \
-                       (const R *)Sbar, (R *)F, Wpart, (R *)rec);
+                       (const R *)Sbar, (R *)F, Wpart, (R *)rec, first ? 1 : 0);
 #define CEN_T(LL, KK, R, CB)                                    \
     if (lanes == 64) { CEN_L(LL, KK, R, CB, 64) }               \
     else if (lanes == 32) { CEN_L(LL, KK, R, CB, 32) }          \
@@ -661,10 +672,10 @@ int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs 
 }
 
 void edge_adjoint_gather(hipStream_t st, bool fp64, int K, const EdgeArgs &a, const CutList &cl, bool want_cbar,
-                         bool make_rslot, const void *rec, void *F, void *cbar) {
+                         bool first, const void *rec, void *F, void *cbar) {
     const int nbn = grid_for(a.n_ext, kRowsPerBlock);
 #define GAT_T(KK, R, CB)                                                                                          \
-    if (make_rslot)                                                                                               \
+    if (first)                                                                                                    \
         hipLaunchKernelGGL((k_adj_gather<KK, R, CB, true>), dim3(nbn), dim3(256), 0, st, a, cl, (const R *)rec,   \
                            (R *)F, (R *)cbar);                                                                    \
     else                                                                                                          \

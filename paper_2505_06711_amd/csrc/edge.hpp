@@ -36,7 +36,10 @@ struct CutList {
     int32_t *fslot, *cpos, *rslot;
     const int32_t *rev;
 };
-void compact_cutoff(hipStream_t st, const EdgeArgs &a, double r_c, CutList &cl);
+// disp (or NULL): the displacement maximum refresh_positions raised; the launch hands it to
+// host_disp (pinned) and clears it for the next step.
+void compact_cutoff(hipStream_t st, const EdgeArgs &a, double r_c, CutList &cl, unsigned long long *disp = nullptr,
+                    double *host_disp = nullptr);
 
 // S[i][lambda][m] for the n local rows.  c: messages of all ext atoms, [n_ext][K].
 void edge_forward(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl, const EdgeConsts &ec,
@@ -47,16 +50,17 @@ void edge_forward(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, co
 // writes at the edge's compacted slot the record of what it gives the neighbour end.
 // Neighbour role (every ext row): sums the records of the row's incoming edges through
 // rslot.
-//   Sbar [n][NL][K] (locals), c [n_ext][K]; F [n_ext][3] is accumulated;
+//   Sbar [n][NL][K] (locals), c [n_ext][K]; F [n_ext][3] is accumulated, or with `first` (the
+// sweep's first layer) set, by the centre role for the locals and by the gather for the ghosts;
 //   cbar [n_ext][K] is overwritten when want_cbar; Wpart receives one FP64 [9] per block
 // of the centre-role launch (the return value is that block count); rec holds
 // edge_record_elems(K) working-type values per (compacted) list slot.
 int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
-                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, void *F, double *Wpart,
-                        void *rec);
-// make_rslot: the first gather after compact_cutoff (fills rslot; later gathers read it).
+                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, bool first, void *F,
+                        double *Wpart, void *rec);
+// first: the first gather after compact_cutoff also fills rslot; later gathers read it.
 void edge_adjoint_gather(hipStream_t st, bool fp64, int K, const EdgeArgs &a, const CutList &cl, bool want_cbar,
-                         bool make_rslot, const void *rec, void *F, void *cbar);
+                         bool first, const void *rec, void *F, void *cbar);
 // Values per edge record: the edge gradient (3, padded to 4) and K adjoint-message terms.
 inline int edge_record_elems(int K) { return 4 + K; }
 int edge_backward_blocks(int64_t n);   // blocks of the centre-role launch over n local rows

@@ -357,6 +357,9 @@ __device__ inline void out_layer(const float *hl, int ldl, const WT *wo, const W
                                  int tid) {
     constexpr int QN = H / PARTS;
     const int row = tid / PARTS, part = tid % PARTS;
+    const int64_t grow = m0 + row;
+    int2 copies = make_int2(0, 0);
+    if (DOUT > 1 && p.copy_rng && grow < p.rows) copies = p.copy_rng[grow];
     A hv[QN];
 #pragma unroll
     for (int j = 0; j < QN; ++j) hv[j] = (A)hl[row * ldl + part * QN + j];
@@ -371,11 +374,20 @@ __device__ inline void out_layer(const float *hl, int ldl, const WT *wo, const W
     }
 #pragma unroll
     for (int o = 0; o < DOUT; ++o) s[o] = sum_lanes<PARTS>(s[o]);
-    const int64_t grow = m0 + row;
-    if (grow < p.rows) {
+    if (grow >= p.rows) return;
 #pragma unroll
-        for (int o = 0; o < DOUT; ++o)
-            if (o % PARTS == part) p.C[grow * p.ldc + o] = (float)(s[o] + (A)bo[o]);
+    for (int o0 = 0; o0 < DOUT; o0 += PARTS) {
+        // the thread's own output of this round, picked by selects so that the stores (and the loop
+        // over the copies) are run once by all threads, not once per output
+        const int o = o0 + part;
+        if (o >= DOUT) break;
+        A so = s[o0];
+#pragma unroll
+        for (int k = 1; k < PARTS && o0 + k < DOUT; ++k) so = part == k ? s[o0 + k] : so;
+        float v = (float)(so + (A)bo[o]);
+        if (DOUT > 1 && p.resid) v = v + p.resid[grow * DOUT + o];
+        p.C[grow * DOUT + o] = v;
+        for (int q = copies.x; q < copies.y; ++q) p.Cg[(int64_t)p.copy_idx[q] * DOUT + o] = v;
     }
 }
 
@@ -470,6 +482,24 @@ __device__ inline void fused_layer(const typename Fuse<OP>::T *X, int ldx, const
 
 }  // namespace
 
+// Multinomial weight l! / (lx! ly! lz!) of Cartesian component q (components by order, then lx, ly
+// descending).
+constexpr float lambda_weight(int L, int q) {
+    int k = 0;
+    for (int l = 0; l <= L; ++l)
+        for (int x = l; x >= 0; --x)
+            for (int y = l - x; y >= 0; --y, ++k)
+                if (k == q) {
+                    int w = 1;
+                    for (int j = 2; j <= l; ++j) w *= j;
+                    for (int j = 2; j <= x; ++j) w /= j;
+                    for (int j = 2; j <= y; ++j) w /= j;
+                    for (int j = 2; j <= l - x - y; ++j) w /= j;
+                    return (float)w;
+                }
+    return 0.0f;
+}
+
 // Density features of order l of tile row r for the pairs (a, b >= a) with a in [A0, A1):
 // X[r][l P + idx(a, b)] = sum over the components q of order l of w_q S[q][a] S[q][b].
 // A tile row past the segment's end takes the segment's last row (its results are never
@@ -483,7 +513,7 @@ __device__ inline void density_part(const FusedNN &p, typename Fuse<OP>::T *X, i
     float sv[nq][K], w[nq];
 #pragma unroll
     for (int q = 0; q < nq; ++q) {
-        w[q] = (float)p.dc.w[q0 + q];
+        w[q] = lambda_weight(L, q0 + q);
 #pragma unroll
         for (int m4 = 0; m4 < K / 4; ++m4) {
             const float4 v4 = Sg[q * (K / 4) + m4];
@@ -673,9 +703,29 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
     // takes column q = tid % H of rows r0, r0 + NT / H, ...
     {
         for (int e = tid; e < dout * H; e += NT) wo[e] = p.Wout[e];
-        for (int e = tid; e < BM * dout; e += NT) {
-            const int r = e / dout, o = e % dout;
-            gs[e] = m0 + r < p.rows ? p.G[(m0 + r) * p.ldg + o] : 0.0f;
+        if (dout == 1) {   // the energy NN: the seed of the reverse sweep
+            for (int r = tid; r < BM; r += NT) {
+                const int64_t row = m0 + r;
+                gs[r] = row < p.rows ? (float)(p.seed_scale * (p.seed_g ? *p.seed_g : 1.0) *
+                                               (p.seed_w ? p.seed_w[p.perm[row]] : 1.0))
+                                     : 0.0f;
+            }
+        } else {
+            for (int e = tid; e < BM * K; e += NT) {
+                const int64_t row = m0 + e / K;
+                const int o = e % K;
+                float g = 0.0f;
+                if (row < p.rows) {
+                    g = p.G[row * K + o];
+                    if (p.copy_rng) {   // the ghost copies' message adjoints
+                        const int2 c = p.copy_rng[row];
+                        for (int q = c.x; q < c.y; ++q) g += p.Gg[(int64_t)p.copy_idx[q] * K + o];
+                    }
+                    if (p.next_in) g = g + p.next_in[row * K + o];
+                    if (p.next_out) p.next_out[row * K + o] = g;
+                }
+                gs[e] = g;
+            }
         }
         constexpr int NR = BM * H / NT, rstep = NT / H;
         const int q = tid % H, r0 = tid / H;
@@ -761,7 +811,7 @@ __device__ __forceinline__ void mlp_bwd_body(const FusedNN &p, const int64_t m0)
             const float4 v4 = Sg[m4];
             sl[4 * m4] = v4.x; sl[4 * m4 + 1] = v4.y; sl[4 * m4 + 2] = v4.z; sl[4 * m4 + 3] = v4.w;
         }
-        const float wl = (float)p.dc.w[lam];
+        const float wl = (L < 2 || lam < 4 || lam == 4 || lam == 7 || lam == 9) ? 1.0f : 2.0f;   // lambda_weight
         // each of the K (K + 1) / 2 distinct matrix entries is read once and used for both
         // (a, b) and (b, a); every acc[a] still receives its terms in the order b = 0 .. K - 1
         float acc2[K];
@@ -928,7 +978,7 @@ static void launch_tiles(hipStream_t st, bool fwd, bool small, unsigned tiles, c
 // Launch the fused kernel over nseg segments of the same NN shape.
 static void launch_fused(hipStream_t st, OpType op, bool fwd, const FusedNN *segs, int nseg) {
     const FusedNN &p = segs[0];
-    const int NLK = p.dc.lstart[p.L + 1] * p.K;
+    const int NLK = n_lambda(p.L) * p.K;
     if (!fused_nn_ok(p.F, p.H, p.nh, p.dout, NLK) || p.F != fused_features(p.L, p.K) ||
         (p.dout != p.K && p.dout != 1))
         fail(REANN_E_DEVICE, "mlp_fused: unsupported layer shape");

@@ -53,7 +53,6 @@ struct FusedNN {
     int64_t rows;                 // rows of this element's segment
     int F, H, nh, dout;           // input width, hidden width, hidden layers, output width
     int L, K;                     // angular order and radial channels of the density input
-    DensityConsts dc;             // its multinomial weights and component ranges
     const float *S;               // orbital sums [rows][NL*K] (the NN input is their density)
     // packed operands (pack_operand): forward, layer k [out][in]; adjoint, its transpose
     const void *W[kFuseMaxNh];
@@ -68,10 +67,25 @@ struct FusedNN {
     float zscale[kFuseMaxNh];
     float hinv[kFuseMaxNh];
     const float *xinv;
-    const float *G;               // adjoint: output adjoint [rows][ldg]
-    int ldg;
-    float *C;                     // forward: outputs [rows][ldc]; adjoint: dE/dS [rows][NL*K]
-    int ldc;
+    // The exchange around a message NN, done by the launch itself.  copy_rng (or NULL: no copies):
+    // row r's ghost copies are copy_idx[copy_rng[r].x .. y).  Forward: the outputs are also written
+    // to the copies' rows of Cg.  Adjoint: the copies' rows of Gg are added to G, in that order.
+    const int2 *copy_rng;
+    const int32_t *copy_idx;
+    float *Cg;
+    const float *Gg;
+    // Radial form's residual (NULL otherwise), [rows][K].  Forward: resid is added to the outputs.
+    // Adjoint: next_in is added to G (after the copies), and the sum is kept in next_out.
+    const float *resid;
+    const float *next_in;
+    float *next_out;
+    // Adjoint of the energy NN (dout = 1), which takes no G: row r's output adjoint is
+    // seed_scale g w[perm[r]] (g = *seed_g or 1; w = seed_w in caller order or 1)
+    double seed_scale;
+    const double *seed_g, *seed_w;
+    const int32_t *perm;
+    const float *G;               // adjoint of a message NN: output adjoint [rows][K]
+    float *C;                     // forward: outputs [rows][dout]; adjoint: dE/dS [rows][NL*K]
 };
 
 // Segments of the same NN shape (the elements' rows of one layer, or locals and ghosts) for

@@ -313,21 +313,23 @@ __global__ void k_energy(int64_t n, double scale, const R *__restrict__ y, const
 }
 
 // The same for a small system in one block, which also forms the total: thread t takes atoms
-// t, t + 256, ... in order, then a tree over the threads.
+// t, t + kEnergyThreads, ... in order, then a tree over the threads.  One block is bound by the
+// loads in series per thread: 256 threads took 9.8 us for 4,000 atoms, 1,024 take 4.2 us.
+constexpr int kEnergyThreads = 1024;
 template <typename R>
-__global__ __launch_bounds__(kRedBlock) void k_energy_total(int64_t n, double scale, const R *__restrict__ y,
+__global__ __launch_bounds__(kEnergyThreads) void k_energy_total(int64_t n, double scale, const R *__restrict__ y,
                                                             const int32_t *__restrict__ perm, const double *__restrict__ w,
                                                             double *__restrict__ Eat, double *__restrict__ total) {
-    __shared__ double sm[kRedBlock];
+    __shared__ double sm[kEnergyThreads];
     double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += kRedBlock) {
+    for (int64_t i = threadIdx.x; i < n; i += kEnergyThreads) {
         const double e = scale * (double)y[i];
         if (Eat) Eat[perm[i]] = e;
         acc += w ? w[perm[i]] * e : e;
     }
     sm[threadIdx.x] = acc;
     __syncthreads();
-    for (int h = kRedBlock / 2; h > 0; h >>= 1) {
+    for (int h = kEnergyThreads / 2; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h) sm[threadIdx.x] += sm[threadIdx.x + h];
         __syncthreads();
     }
@@ -337,8 +339,8 @@ __global__ __launch_bounds__(kRedBlock) void k_energy_total(int64_t n, double sc
 void energy_total(hipStream_t st, bool fp64, int64_t n, double scale, const void *y, const int32_t *perm,
                   const double *w_user, double *Eat_user, double *partials, double *total) {
     if (n <= kEnergyOneBlock) {
-        if (fp64) hipLaunchKernelGGL(k_energy_total<double>, dim3(1), dim3(kRedBlock), 0, st, n, scale, (const double *)y, perm, w_user, Eat_user, total);
-        else hipLaunchKernelGGL(k_energy_total<float>, dim3(1), dim3(kRedBlock), 0, st, n, scale, (const float *)y, perm, w_user, Eat_user, total);
+        if (fp64) hipLaunchKernelGGL(k_energy_total<double>, dim3(1), dim3(kEnergyThreads), 0, st, n, scale, (const double *)y, perm, w_user, Eat_user, total);
+        else hipLaunchKernelGGL(k_energy_total<float>, dim3(1), dim3(kEnergyThreads), 0, st, n, scale, (const float *)y, perm, w_user, Eat_user, total);
         LAUNCH_OK("k_energy_total");
         return;
     }
@@ -467,29 +469,28 @@ void out_layer_vjp(hipStream_t st, int64_t rows, int out, int in, const float *G
     LAUNCH_OK("k_out_vjp");
 }
 
-// The backward's start: the energy adjoint of every atom, and (nz > 0) zeros in z[0, nz).
+// The backward's start on the per-layer path: the energy adjoint of every atom.
 template <typename R>
 __global__ void k_seed(int64_t n, double scale, const double *__restrict__ g, const int32_t *__restrict__ perm,
-                       const double *__restrict__ w, R *__restrict__ ybar, int64_t nz, R *__restrict__ z) {
+                       const double *__restrict__ w, R *__restrict__ ybar) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) ybar[i] = R(scale * (g ? *g : 1.0) * (w ? w[perm[i]] : 1.0));
-    if (i < nz) z[i] = R(0);
 }
 
 void fill_energy_seed(hipStream_t st, bool fp64, int64_t n, double scale, const double *g, const int32_t *perm,
-                      const double *w_user, void *ybar, int64_t nzero, void *zero_out) {
-    const int64_t nt = std::max<int64_t>(n, nzero);
+                      const double *w_user, void *ybar) {
     if (fp64)
-        hipLaunchKernelGGL(k_seed<double>, dim3(grid_for(nt, 256)), dim3(256), 0, st, n, scale, g, perm, w_user,
-                           (double *)ybar, nzero, (double *)zero_out);
+        hipLaunchKernelGGL(k_seed<double>, dim3(grid_for(n, 256)), dim3(256), 0, st, n, scale, g, perm, w_user,
+                           (double *)ybar);
     else
-        hipLaunchKernelGGL(k_seed<float>, dim3(grid_for(nt, 256)), dim3(256), 0, st, n, scale, g, perm, w_user,
-                           (float *)ybar, nzero, (float *)zero_out);
+        hipLaunchKernelGGL(k_seed<float>, dim3(grid_for(n, 256)), dim3(256), 0, st, n, scale, g, perm, w_user,
+                           (float *)ybar);
     LAUNCH_OK("k_seed");
 }
 
 // Blocks [0, 9): virial component q = the sum over the nw rows of Wpart[.][q] (in the order of
-// sum_rows), times g, to Wout (when asked for); the other blocks: forces in caller order, times g.
+// sum_rows) to Wout (when asked for); the other blocks: forces in caller order, each with its
+// ghost copies' forces.
 __device__ inline double virial_column(const double *__restrict__ part, int nw, int q) {
     __shared__ double sm[256];
     double s8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -507,29 +508,67 @@ __device__ inline double virial_column(const double *__restrict__ part, int nw, 
     return sm[0];
 }
 
+// Many rows of partials: block b sums its share of consecutive rows into out[b][0 .. 9).  Threads
+// 0 .. 251 read the share as one contiguous run, 28 rows at a time (thread t always has column
+// t % 9); the 28 sums of a column are then added in order.  Nine blocks reading a column each
+// (72-byte strides) took 205 us of a 1.2M-atom step (226,000 rows) and 19.6 us of a 100,800-atom
+// one; this and the final blocks take 12.5 + 29 us (4.9 + 6.7), the forces and the ghosts'
+// share of them included.
+__global__ __launch_bounds__(256) void k_virial_part(const double *__restrict__ part, int nw, double *__restrict__ out) {
+    __shared__ double sm[252];
+    const int per = (nw + gridDim.x - 1) / gridDim.x;
+    const int64_t e0 = (int64_t)min(nw, (int)blockIdx.x * per) * 9, e1 = (int64_t)min(nw, ((int)blockIdx.x + 1) * per) * 9;
+    const int t = threadIdx.x;
+    if (t < 252) {
+        double s4[4] = {0.0, 0.0, 0.0, 0.0};
+        int64_t e = e0 + t;
+        for (; e + 3 * 252 < e1; e += 4 * 252)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s4[u] += part[e + u * 252];
+        for (; e < e1; e += 252) s4[0] += part[e];
+        sm[t] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    }
+    __syncthreads();
+    if (t < 9) {
+        double w = 0.0;
+        for (int r = 0; r < 28; ++r) w += sm[9 * r + t];
+        out[9 * blockIdx.x + t] = w;
+    }
+}
+
 template <typename R>
 __global__ __launch_bounds__(256) void k_forces_out(int64_t n, const R *__restrict__ F, const int32_t *__restrict__ perm,
-                                                    const double *__restrict__ g, double *__restrict__ out,
+                                                    const int2 *__restrict__ copy_rng,
+                                                    const int32_t *__restrict__ copy_idx, double *__restrict__ out,
                                                     const double *__restrict__ Wpart, int nw, double *__restrict__ Wout) {
-    const double gs = g ? *g : 1.0;
     if (blockIdx.x < 9) {
         if (!Wout) return;   // uniform over the block
         const double w = virial_column(Wpart, nw, (int)blockIdx.x);
-        if (threadIdx.x == 0) Wout[blockIdx.x] = gs * w;
+        if (threadIdx.x == 0) Wout[blockIdx.x] = w;
         return;
     }
     const int64_t t = (int64_t)(blockIdx.x - 9) * blockDim.x + threadIdx.x;
     if (t < n * 3) {
         const int64_t i = t / 3, a = t % 3;
-        out[(int64_t)perm[i] * 3 + a] = gs * (double)F[t];
+        R f = F[t];
+        const int2 c = copy_rng[i];
+        for (int q = c.x; q < c.y; ++q) f += F[(n + copy_idx[q]) * 3 + a];
+        out[(int64_t)perm[i] * 3 + a] = (double)f;
     }
 }
 
-void forces_out(hipStream_t st, bool fp64, int64_t n, const void *F, const int32_t *perm, const double *g,
-                double *forces_user, const double *Wpart, int nw, double *virial_out) {
+void forces_out(hipStream_t st, bool fp64, int64_t n, const void *F, const int32_t *perm, const int2 *copy_rng,
+                const int32_t *copy_idx, double *forces_user, double *Wpart, int nw, double *virial_out) {
+    if (virial_out && nw > kVirialRows) {
+        double *sums = Wpart + (int64_t)nw * 9;
+        hipLaunchKernelGGL(k_virial_part, dim3(kVirialBlocks), dim3(256), 0, st, Wpart, nw, sums);
+        LAUNCH_OK("k_virial_part");
+        Wpart = sums;
+        nw = kVirialBlocks;
+    }
     const unsigned nb = 9u + (unsigned)grid_for(n * 3, 256);
-    if (fp64) hipLaunchKernelGGL(k_forces_out<double>, dim3(nb), dim3(256), 0, st, n, (const double *)F, perm, g, forces_user, Wpart, nw, virial_out);
-    else hipLaunchKernelGGL(k_forces_out<float>, dim3(nb), dim3(256), 0, st, n, (const float *)F, perm, g, forces_user, Wpart, nw, virial_out);
+    if (fp64) hipLaunchKernelGGL(k_forces_out<double>, dim3(nb), dim3(256), 0, st, n, (const double *)F, perm, copy_rng, copy_idx, forces_user, Wpart, nw, virial_out);
+    else hipLaunchKernelGGL(k_forces_out<float>, dim3(nb), dim3(256), 0, st, n, (const float *)F, perm, copy_rng, copy_idx, forces_user, Wpart, nw, virial_out);
     LAUNCH_OK("k_forces_out");
 }
 

@@ -54,13 +54,16 @@ void energy_total(hipStream_t st, bool fp64, int64_t n, double scale, const void
 // out[0] = sum of partials[0..nb) (single block, fixed order); if accumulate, out[q] += ...
 void sum_rows(hipStream_t st, const double *partials, int nb, int width, double *out, bool accumulate);
 // ybar[i] = scale * g * w[perm[i]]  (g = device scalar or NULL = 1; w_user = caller-order weights
-// or NULL = 1), and zero_out[0, nzero) = 0 in the same launch (working type)
+// or NULL = 1)
 void fill_energy_seed(hipStream_t st, bool fp64, int64_t n, double scale, const double *g, const int32_t *perm,
-                      const double *w_user, void *ybar, int64_t nzero = 0, void *zero_out = nullptr);
-// forces_user[perm[i]][a] = gscale * F[i][a]; virial_out[q] = gscale * sum_r Wpart[r][q] over the
-// nw rows of partials (virial_out NULL: not formed); one launch
-void forces_out(hipStream_t st, bool fp64, int64_t n, const void *F, const int32_t *perm, const double *g,
-                double *forces_user, const double *Wpart, int nw, double *virial_out);
+                      const double *w_user, void *ybar);
+// forces_user[perm[i]][a] = F[i][a] + the ghost copies' F (copy_idx[copy_rng[i].x .. y), in that
+// order); virial_out[q] = sum_r Wpart[r][q] over the nw rows of partials (virial_out NULL: not
+// formed).  One launch for up to kVirialRows rows of partials; more are first summed in
+// kVirialBlocks blocks, whose rows go behind the nw rows of Wpart.
+constexpr int kVirialRows = 2048, kVirialBlocks = 128;
+void forces_out(hipStream_t st, bool fp64, int64_t n, const void *F, const int32_t *perm, const int2 *copy_rng,
+                const int32_t *copy_idx, double *forces_user, double *Wpart, int nw, double *virial_out);
 void zero(hipStream_t st, void *p, size_t bytes);
 // dst += src, and dst = src, over `count` elements of the working type (FP64 or FP32)
 void add_into(hipStream_t st, bool fp64, int64_t count, void *dst, const void *src);

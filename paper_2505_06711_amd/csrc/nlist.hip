@@ -837,33 +837,58 @@ void check_deferred(NListScratch &s) {
 
 // ------------------------------------------------------------ per-step work --
 
-__global__ void k_refresh(Geom g, int64_t n, int64_t n_ext, const double *__restrict__ pos, const int32_t *__restrict__ perm,
-                          const int32_t *__restrict__ q, const int32_t *__restrict__ gh_owner,
-                          const int32_t *__restrict__ gh_shift, double4 *__restrict__ p4) {
-    int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= n_ext) return;
-    int64_t i = x < n ? x : gh_owner[x - n];
-    int64_t u = perm[i];
-    double w[3];
-    for (int a = 0; a < 3; ++a) {
-        double v = pos[3 * u + a];
-        if (g.per[a]) {
-            double t = (double)q[3 * u + a] * g.L[a];   // q is stored per caller index
-            v = v - t;
+// With disp, the skin check rides along: the largest displacement since the list build.  A block
+// raises the maximum only if its own is larger than what it reads there, so that few blocks meet
+// at the word.
+__global__ __launch_bounds__(256) void k_refresh(Geom g, int64_t n, int64_t n_ext, const double *__restrict__ pos,
+                                                 const int32_t *__restrict__ perm, const int32_t *__restrict__ q,
+                                                 const int32_t *__restrict__ gh_owner,
+                                                 const int32_t *__restrict__ gh_shift, double4 *__restrict__ p4,
+                                                 const double *__restrict__ xref, unsigned long long *disp) {
+    __shared__ unsigned long long sm[4];
+    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    unsigned long long d2bits = 0;
+    if (x < n_ext) {
+        int64_t i = x < n ? x : gh_owner[x - n];
+        int64_t u = perm[i];
+        double w[3], d2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            double v = pos[3 * u + a];
+            if (disp && x < n) {
+                const double d = v - xref[3 * x + a];
+                d2 += d * d;
+            }
+            if (g.per[a]) {
+                double t = (double)q[3 * u + a] * g.L[a];   // q is stored per caller index
+                v = v - t;
+            }
+            w[a] = v;
         }
-        w[a] = v;
+        d2bits = (unsigned long long)__double_as_longlong(d2) & 0x7fffffffffffffffull;
+        if (x >= n) {
+            int64_t gi = x - n;
+            for (int a = 0; a < 3; ++a)
+                if (g.per[a]) w[a] = w[a] + (double)gh_shift[3 * gi + a] * g.L[a];
+        }
+        p4[x] = make_double4(w[0], w[1], w[2], 0.0);
     }
-    if (x >= n) {
-        int64_t gi = x - n;
-        for (int a = 0; a < 3; ++a)
-            if (g.per[a]) w[a] = w[a] + (double)gh_shift[3 * gi + a] * g.L[a];
+    if (!disp) return;   // uniform over the grid
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long t = __shfl_xor(d2bits, o, 64);
+        d2bits = t > d2bits ? t : d2bits;
     }
-    p4[x] = make_double4(w[0], w[1], w[2], 0.0);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = d2bits;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int v = 1; v < 4; ++v) d2bits = sm[v] > d2bits ? sm[v] : d2bits;
+        if (d2bits > __hip_atomic_load(disp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(disp, d2bits);
+    }
 }
 
-void refresh_positions(hipStream_t st, const NList &nl, const double *d_pos, double4 *p4) {
+void refresh_positions(hipStream_t st, const NList &nl, const double *d_pos, double4 *p4, unsigned long long *disp) {
     hipLaunchKernelGGL(k_refresh, dim3(grid_for(nl.n_ext, 256)), dim3(256), 0, st, nl.g, nl.n, nl.n_ext, d_pos,
-                       nl.perm.ptr(), nl.q.ptr(), nl.gh_owner.ptr(), nl.gh_shift.ptr(), p4);
+                       nl.perm.ptr(), nl.q.ptr(), nl.gh_owner.ptr(), nl.gh_shift.ptr(), p4, nl.xref.ptr(), disp);
     LAUNCH_OK("k_refresh");
 }
 

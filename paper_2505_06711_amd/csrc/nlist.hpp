@@ -70,8 +70,11 @@ void check_deferred(NListScratch &s);
 // Positions of the extended system from caller positions: w_i = x_{perm i} - q_i L for
 // locals, owner position + shift L for ghosts.  SoA output px/py/pz [n_ext].
 // Wrapped positions of all ext atoms (locals then ghost copies) as (x, y, z, 0), one 32-byte
-// record per atom so that a neighbour's position is a single cache line.
-void refresh_positions(hipStream_t st, const NList &nl, const double *d_pos, double4 *p4);
+// record per atom so that a neighbour's position is a single cache line.  disp (or NULL): raised to
+// the largest |x_i - xref_i|^2 over the locals, as the bits of a double (a NaN, whose bits lie
+// above +inf's, counts as too far); the caller clears it.
+void refresh_positions(hipStream_t st, const NList &nl, const double *d_pos, double4 *p4,
+                       unsigned long long *disp = nullptr);
 
 // max_i |x_i - xref_i|^2 over locals -> d_out[0]; d_out holds 1 + 1024 doubles (partials after it).
 void max_displacement2(hipStream_t st, const NList &nl, const double *d_pos, double *d_out);

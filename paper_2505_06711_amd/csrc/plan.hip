@@ -307,7 +307,7 @@ void Plan::alloc_buffers() {
     Z.ensure((size_t)T * nh * ns * H * rs);
     if (!fused()) Hh.ensure((size_t)2 * ns * H * rs);
     y.ensure((size_t)n * K * rs);
-    ybar.ensure((size_t)n * rs);
+    if (!fused()) ybar.ensure((size_t)n * rs);
     Eat.ensure((size_t)n * 8);
     Epart.ensure((size_t)(grid_for(n, 256) + 1) * 8);
     Sbar.ensure((size_t)ns * NL * K * rs);
@@ -320,7 +320,7 @@ void Plan::alloc_buffers() {
     }
     cbar.ensure((size_t)ne * K * rs);
     this->F.ensure((size_t)ne * 3 * rs);
-    Wpart.ensure((size_t)T * (edge_backward_blocks(n) + 1) * 9 * 8);   // per layer, summed once
+    Wpart.ensure((size_t)(T * (edge_backward_blocks(n) + 1) + kVirialBlocks) * 9 * 8);   // per layer, summed once
     disp.ensure(1025 * 8);
     col2.ensure((size_t)(nl.n_pairs + 1) * 4);
     fslot.ensure((size_t)(nl.n_pairs + 1) * 4);
@@ -334,7 +334,7 @@ void Plan::alloc_buffers() {
 size_t Plan::device_bytes() const {
     size_t b = 0;
     for (const DevBuf *d : {&p4, &c, &S, &rho, &Z, &Hh, &y, &ybar, &Eat, &Epart, &Sbar, &rhobar, &gA, &gB,
-                            &cbar, &F, &Wpart, &disp, &col2, &fslot, &cpos, &rslot, &nloc, &ngh, &erec, &fp8s,
+                            &cbar, &F, &Wpart, &disp, &check_word, &col2, &fslot, &cpos, &rslot, &nloc, &ngh, &erec, &fp8s,
                             &fp8tmp, &cbar_next})
         b += d->bytes;
     b += nl.perm.bytes() + nl.inv_perm.bytes() + nl.q.bytes() + nl.gh_owner.bytes() + nl.gh_shift.bytes() +
@@ -396,7 +396,7 @@ int Plan::nn_forward(hipStream_t st, int t, bool energy) {
         if (fused()) {
             FusedNN f{};
             f.rows = rows; f.F = F; f.H = H; f.nh = nh; f.dout = dout;
-            f.L = m->L; f.K = K; f.dc = m->density_consts();
+            f.L = m->L; f.K = K;
             f.S = (const float *)(Sptr(t) + (size_t)a * m->NL * K * rs);
             for (int k = 0; k < nh; ++k) {
                 const size_t qi = (size_t)nn_index * nh + k;
@@ -414,7 +414,15 @@ int Plan::nn_forward(hipStream_t st, int t, bool energy) {
                 f.Wout64 = p64 + lay.w_off[nh];
                 f.bout64 = p64 + lay.b_off[nh];
             }
-            f.C = (float *)out; f.ldc = dout;
+            f.C = (float *)out;
+            if (!energy) {
+                if (!nodefeat) {   // the ghosts receive their owners' messages from the launch
+                    f.copy_rng = nl.copy_rng.ptr() + a;
+                    f.copy_idx = nl.copy_idx.ptr();
+                    f.Cg = (float *)(cptr(t + 1) + (size_t)n * K * rs);
+                }
+                if (radial()) f.resid = (const float *)(cptr(t) + (size_t)a * K * rs);   // c^{t+1} = c^t + NN(x^t)
+            }
             segs.push_back(f);
             continue;
         }
@@ -453,8 +461,10 @@ int Plan::nn_forward(hipStream_t st, int t, bool energy) {
 }
 
 // VJP of the NN applied at layer t (energy NN if `energy`), from output adjoint gout
-// [n][ldg] to Sbar when the NN is fused (the density adjoint included), else to rhobar.
-int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg) {
+// [n][ldg] to Sbar when the NN is fused (the density adjoint included), else to rhobar.  The
+// fused kernel forms the energy NN's output adjoint itself (from d_g) and, for a message NN,
+// adds the ghosts' message adjoints and the radial form's residual adjoint to gout.
+int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g) {
     DeviceWeights &w = m->weights(ctx->device, st);
     const NNLayout &lay = energy ? m->en_nn : m->msg_nn;
     const char *blob = energy ? (fp64 ? w.en64.as<char>() : w.en32.as<char>())
@@ -483,7 +493,7 @@ int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg) 
         if (fused()) {
             FusedNN f{};
             f.rows = rows; f.F = F; f.H = H; f.nh = nh; f.dout = lay.dout[nh];
-            f.L = m->L; f.K = m->K; f.dc = m->density_consts();
+            f.L = m->L; f.K = m->K;
             f.S = (const float *)(Sptr(t) + (size_t)a * m->NL * m->K * rs);
             for (int k = 0; k < nh; ++k) {
                 const size_t qi = (size_t)nn_index * nh + k;
@@ -491,8 +501,26 @@ int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg) 
                 f.Z[k] = (float *)(Zptr(t, k) + (size_t)a * H * rs);
             }
             f.Wout = (const float *)(p + lay.w_off[nh] * rs);
-            f.G = (const float *)gin; f.ldg = ldin;
-            f.C = (float *)(Sbar.as<char>() + (size_t)a * m->NL * m->K * rs); f.ldc = m->NL * m->K;
+            if (energy) {
+                f.seed_scale = m->energy_scale;
+                f.seed_g = d_g;
+                f.seed_w = have_ew ? d_ew.ptr() : nullptr;
+                f.perm = nl.perm.ptr() + a;
+            } else {
+                const int K = m->K;
+                f.G = (const float *)gin;
+                if (!nodefeat) {
+                    f.copy_rng = nl.copy_rng.ptr() + a;
+                    f.copy_idx = nl.copy_idx.ptr();
+                    f.Gg = (const float *)(gout + (size_t)n * K * rs);
+                }
+                if (radial()) {   // t is the layer of the NN: c^{t+1} reaches E through c^{t+2} too
+                    float *next = (float *)(cbar_next.as<char>() + (size_t)a * K * rs);
+                    f.next_in = t + 1 < T - 1 ? next : nullptr;
+                    f.next_out = t > 0 ? next : nullptr;
+                }
+            }
+            f.C = (float *)(Sbar.as<char>() + (size_t)a * m->NL * m->K * rs);
             segs.push_back(f);
             seg_op = bop;
             continue;
@@ -660,18 +688,15 @@ void Plan::forward(const double *d_pos, double *d_energy, double *d_atom_energy,
     TraceRange range("reann: forward");
     mark(st, -1);
     if (auto_list && built && !(fp8_fused() && !fp8_ready)) {
-        // The skin check goes to the device with the forward on the list it checks behind it,
-        // and its answer is read while that forward runs, so the device does not wait for the
+        // The skin check rides on the forward's first two launches, on the list it checks, and its
+        // answer is read while the rest of that forward runs, so the device does not wait for the
         // host between the check and the forward.  A stale list is rebuilt and the forward
         // enqueued again: its outputs are written again, in stream order.  (On a stale list
         // the first forward only misses pairs; every index it uses is the old list's own.)
-        max_displacement2(st, nl, d_pos, disp.as<double>());
-        double *h = check_host.get_double();
-        HIP_OK(hipMemcpyAsync(h, disp.p, 8, hipMemcpyDeviceToHost, st));
+        const double *h = check_host.get_double();
+        if (!check_word.p) zero(st, check_word.ensure(8), 8);
         if (!check_ev) HIP_OK(hipEventCreateWithFlags(&check_ev, hipEventDisableTiming));
-        HIP_OK(hipEventRecord(check_ev, st));
-        mark(st, PH_NLIST, 0);
-        launch_forward(d_pos, d_energy, d_atom_energy, st);
+        launch_forward(d_pos, d_energy, d_atom_energy, st, true);
         HIP_OK(hipEventSynchronize(check_ev));
         check_deferred();
         const double half = 0.5 * skin;
@@ -686,11 +711,12 @@ void Plan::forward(const double *d_pos, double *d_energy, double *d_atom_energy,
     launch_forward(d_pos, d_energy, d_atom_energy, st);
 }
 
-void Plan::launch_forward(const double *d_pos, double *d_energy, double *d_atom_energy, hipStream_t st) {
+void Plan::launch_forward(const double *d_pos, double *d_energy, double *d_atom_energy, hipStream_t st, bool check) {
     if (!built) fail(REANN_E_STATE, "neighbour list not built");
     const int K = m->K;
     DeviceWeights &w = m->weights(ctx->device, st);
-    refresh_positions(st, nl, d_pos, p4.as<double4>());
+    unsigned long long *word = check ? check_word.as<unsigned long long>() : nullptr;
+    refresh_positions(st, nl, d_pos, p4.as<double4>(), word);
     // c^0 depends on the element alone and nothing writes it afterwards: set once per list build
     if (c0_build != rebuilds) {
         init_messages(st, fp64, nl.n_ext, K, nl.spec_ext.ptr(), fp64 ? w.c064.p : w.c032.p, cptr(0));
@@ -698,7 +724,8 @@ void Plan::launch_forward(const double *d_pos, double *d_energy, double *d_atom_
     }
     EdgeArgs ea{n, nl.n_ext, nl.row.ptr(), nl.col.ptr(), p4.as<double4>()};
     CutList cl = cutlist();
-    compact_cutoff(st, ea, m->r_c, cl);
+    compact_cutoff(st, ea, m->r_c, cl, word, check ? check_host.get_double() : nullptr);
+    if (check) HIP_OK(hipEventRecord(check_ev, st));
     const EdgeConsts ec = m->edge_consts();
     const DensityConsts dc = m->density_consts();
     mark(st, PH_OTHER);
@@ -721,11 +748,11 @@ void Plan::launch_forward(const double *d_pos, double *d_energy, double *d_atom_
         }
         if (t < T - 1) {
             mark(st, PH_NN_FWD, nn_forward(st, t, false));
-            if (radial()) {   // c^{t+1} = c^t + NN(x^t) for the rows the NN ran over
+            if (radial() && !fused()) {   // c^{t+1} = c^t + NN(x^t) for the rows the NN ran over
                 add_into(st, fp64, nS() * K, cptr(t + 1), cptr(t));
                 mark(st, PH_OTHER);
             }
-            if (!nodefeat) {
+            if (!nodefeat && !fused()) {
                 ghost_gather(st, fp64, n, nl.n_gh, K, nl.gh_owner.ptr(), cptr(t + 1));
                 mark(st, PH_GHOST);
             }
@@ -748,11 +775,11 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
     const EdgeConsts ec = m->edge_consts();
     const DensityConsts dc = m->density_consts();
     mark(st, -1);
-    // the energy adjoints, and the force accumulator cleared, in one launch
-    fill_energy_seed(st, fp64, n, m->energy_scale, d_g, nl.perm.ptr(), have_ew ? d_ew.ptr() : nullptr, ybar.p,
-                     nl.n_ext * 3, this->F.p);
-    mark(st, PH_OTHER);
-    mark(st, PH_NN_BWD, nn_vjp(st, T - 1, true, ybar.as<char>(), 1));
+    if (!fused()) {   // the energy adjoints (the fused energy NN forms them itself)
+        fill_energy_seed(st, fp64, n, m->energy_scale, d_g, nl.perm.ptr(), have_ew ? d_ew.ptr() : nullptr, ybar.p);
+        mark(st, PH_OTHER);
+    }
+    mark(st, PH_NN_BWD, nn_vjp(st, T - 1, true, ybar.as<char>(), 1, d_g));
     if (!fused() && !radial()) {
         if (m->form == REANN_FORM_DIAG) density_sq_vjp(st, fp64, m->L, K, n, dc, Sptr(T - 1), rhobar.p, Sbar.p);
         else density_vjp(st, fp64, m->L, K, n, dc, Sptr(T - 1), rhobar.p, Sbar.p);
@@ -761,26 +788,26 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
     // the centre role's per-block virial partials of the T layers side by side, summed once
     int nbw = 0;
     for (int t = T - 1; t >= 0; --t) {
-        const int nb = edge_adjoint_centre(st, fp64, m->L, K, ea, cl, ec, cptr(t), Sbar.p, t > 0, this->F.p,
+        const int nb = edge_adjoint_centre(st, fp64, m->L, K, ea, cl, ec, cptr(t), Sbar.p, t > 0, t == T - 1, this->F.p,
                                            Wpart.as<double>() + (size_t)nbw * 9, erec.p);
         nbw += nb;
         mark(st, PH_ADJ_CENTRE, 1);
         edge_adjoint_gather(st, fp64, K, ea, cl, t > 0, t == T - 1, erec.p, this->F.p, cbar.p);
         mark(st, PH_ADJ_GATHER, 1);
         if (t > 0) {
-            // message exchange: the ghosts' message adjoints go back to their owners here;
-            // node-feature exchange: the ghosts keep theirs (their message NN ran locally) and
+            // message exchange: the ghosts' message adjoints go back to their owners here (the
+            // fused message NN adds them itself); node-feature exchange: the ghosts keep theirs (their message NN ran locally) and
             // the adjoints of their orbital sums go back after the NN's VJP
-            if (!nodefeat) {
+            if (!nodefeat && !fused()) {
                 ghost_reduce(st, fp64, n, K, nl.copy_rng.ptr(), nl.copy_idx.ptr(), cbar.p);
                 mark(st, PH_GHOST);
             }
-            if (radial()) {   // c^t also reaches E through c^{t+1} = c^t + NN(x^t) (t < T - 1)
+            if (radial() && !fused()) {   // c^t also reaches E through c^{t+1} = c^t + NN(x^t) (t < T - 1)
                 if (t < T - 1) add_into(st, fp64, nS() * K, cbar.p, cbar_next.p);
                 if (t > 1) copy_into(st, fp64, nS() * K, cbar_next.p, cbar.p);
                 mark(st, PH_OTHER);
             }
-            mark(st, PH_NN_BWD, nn_vjp(st, t - 1, false, cbar.as<char>(), K));
+            mark(st, PH_NN_BWD, nn_vjp(st, t - 1, false, cbar.as<char>(), K, nullptr));
             if (!fused() && !radial()) {
                 if (m->form == REANN_FORM_DIAG)
                     density_sq_vjp(st, fp64, m->L, K, nS(), dc, Sptr(t - 1), rhobar.p, Sbar.p);
@@ -794,11 +821,10 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
             }
         }
     }
-    ghost_reduce(st, fp64, n, 3, nl.copy_rng.ptr(), nl.copy_idx.ptr(), this->F.p);
-    mark(st, PH_GHOST);
-    // the seed carried g; forces are -dE/dx already scaled; the virial partials are summed in the
-    // same launch
-    forces_out(st, fp64, n, this->F.p, nl.perm.ptr(), nullptr, d_forces, Wpart.as<double>(), nbw, d_virial);
+    // the seed carried g; forces are -dE/dx already scaled; the ghosts' forces go back to their
+    // owners and the virial partials are summed in the same launch
+    forces_out(st, fp64, n, this->F.p, nl.perm.ptr(), nl.copy_rng.ptr(), nl.copy_idx.ptr(), d_forces,
+               Wpart.as<double>(), nbw, d_virial);
     mark(st, PH_OTHER);
     if (timing) ++timed_steps;
 }

@@ -147,8 +147,9 @@ struct Plan {
     bool prepare(const double *d_pos, hipStream_t st);
     // false: forwards neither check the skin rule nor rebuild (reann_plan_set_list_policy)
     bool auto_list = true;
-    // the skin check of a forward on a built list: its result copied to the host, and the
-    // event after the copy
+    // the skin check of a forward on a built list: the maximum raised on the device, where the
+    // host receives it, and the event after that
+    DevBuf check_word;
     PinnedWord check_host;
     hipEvent_t check_ev = nullptr;
     // the two halves of prepare: the skin check alone (true if the list was never built or an
@@ -159,8 +160,10 @@ struct Plan {
     // caller's next wait for the stream) instead of by a wait here
     void rebuild(const double *d_pos, hipStream_t st, bool defer_check = false);
     void check_deferred() { reann::check_deferred(ns); }
-    // the forward's launches only: no synchronisation and no allocation, so it can be captured
-    void launch_forward(const double *d_pos, double *d_energy, double *d_atom_energy, hipStream_t st);
+    // the forward's launches only: no synchronisation and no allocation, so it can be captured;
+    // with `check`, the skin check rides along (check_host, valid after check_ev)
+    void launch_forward(const double *d_pos, double *d_energy, double *d_atom_energy, hipStream_t st,
+                        bool check = false);
     size_t device_bytes() const;
     void backward(const double *d_g, double *d_forces, double *d_virial, hipStream_t st);
     void get(int what, int t, double *host);
@@ -193,7 +196,7 @@ struct Plan {
     bool fused() const;
     // both return the launches of the fused NN kernel (0 on the per-layer path)
     int nn_forward(hipStream_t st, int t, bool energy);
-    int nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg);
+    int nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g);
     void mark(hipStream_t st, int phase, int nlaunch = 0);
     CutList cutlist() {
         return CutList{nl.row.ptr(),        col2.as<int32_t>(),  nloc.as<int32_t>(), ngh.as<int32_t>(),
