@@ -687,7 +687,7 @@ struct TraceRange {
 void Plan::forward(const double *d_pos, double *d_energy, double *d_atom_energy, hipStream_t st) {
     TraceRange range("reann: forward");
     mark(st, -1);
-    if (auto_list && built && !(fp8_fused() && !fp8_ready)) {
+    if (auto_list && built && !expect_stale && !(fp8_fused() && !fp8_ready)) {
         // The skin check rides on the forward's first two launches, on the list it checks, and its
         // answer is read while the rest of that forward runs, so the device does not wait for the
         // host between the check and the forward.  A stale list is rebuilt and the forward
@@ -701,12 +701,15 @@ void Plan::forward(const double *d_pos, double *d_energy, double *d_atom_energy,
         check_deferred();
         const double half = 0.5 * skin;
         if (*h <= half * half) return;
+        expect_stale = true;
         rebuild(d_pos, st);
         mark(st, PH_NLIST, 1);
         launch_forward(d_pos, d_energy, d_atom_energy, st);
         return;
     }
+    const bool had_list = built;
     const bool rebuilt = auto_list ? prepare(d_pos, st) : false;
+    expect_stale = rebuilt && had_list;
     mark(st, PH_NLIST, rebuilt ? 1 : 0);
     launch_forward(d_pos, d_energy, d_atom_energy, st);
 }

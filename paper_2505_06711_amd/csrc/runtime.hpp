@@ -152,6 +152,9 @@ struct Plan {
     DevBuf check_word;
     PinnedWord check_host;
     hipEvent_t check_ev = nullptr;
+    // the last forward found its list stale: the next one (an unrelated frame, perhaps) asks first
+    // instead of running a forward on the old list beside the question
+    bool expect_stale = false;
     // the two halves of prepare: the skin check alone (true if the list was never built or an
     // atom has moved more than skin/2 since), and the rebuild (with the FP8 calibration the
     // first time), which allocates
