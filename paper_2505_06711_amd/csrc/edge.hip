@@ -41,14 +41,26 @@ template <int L> struct LamTab {
     }
 };
 
-// Radial Gaussian exp(-alpha x^2).  FP32: 2^(-alpha log2(e) x^2) with the hardware base-2
-// exponential (a single instruction; the exponent carries the same FP32 rounding as the
-// product it replaces).  FP64: exp.  `a` is the matching constant of EdgeConsts.
-__device__ inline float gauss(float a2, float x) { return __builtin_amdgcn_exp2f(-a2 * x * x); }
-__device__ inline double gauss(double a, double x) { return exp(-a * x * x); }
-template <typename R> __device__ inline R gauss_const(const EdgeConsts &ec, int m) {
-    return sizeof(R) == 4 ? R(ec.alphas2[m]) : R(ec.alphas[m]);
+// Radial Gaussian exp(-alpha (r - c)^2) from x = r - c.  FP32: 2^(-alpha log2(e) x^2) with the
+// hardware base-2 exponential (a single instruction).  The centre rounded to FP32 (x is taken
+// from it) would shift every Gaussian of every edge the same way, which the virial of a crystal, a
+// small remainder of cancelling terms, shows most (6,912 rattled Cu atoms, T = 3: relative error of W
+// up to 9.0e-6, 1.2e-6 with this and times_const): with c = c_hi + c_lo the exponent
+// -a (x - c_lo)^2 is x (b - a x) with b = 2 a c_lo, but for the square of c_lo, at no extra
+// instruction.  FP64: exp, b = 0.
+template <typename R> struct Radial { R c, a, b; };
+template <typename R> __device__ inline Radial<R> radial(const EdgeConsts &ec, int m) {
+    if constexpr (sizeof(R) == 4) return Radial<R>{ec.c32[m], ec.a32[m], ec.b32[m]};
+    else return Radial<R>{ec.centres[m], ec.alphas[m], 0.0};
 }
+__device__ inline float gauss(const Radial<float> &g, float x) {
+    return __builtin_amdgcn_exp2f(x * fmaf(-g.a, x, g.b));
+}
+__device__ inline double gauss(const Radial<double> &g, double x) { return exp(-g.a * x * x); }
+// The derivative of the exponent by r (the FP32 form: over ln 2)
+__device__ inline float gauss_slope(const Radial<float> &g, float x) { return fmaf(-g.a, x, fmaf(-g.a, x, g.b)); }
+__device__ inline double gauss_slope(const Radial<double> &g, double x) { return -2.0 * g.a * x; }
+template <typename R> constexpr double kSlopeUnit = sizeof(R) == 4 ? 0.69314718055994531 : 1.0;
 __device__ inline float d_cospi(float x) { return cospif(x); }
 __device__ inline double d_cospi(double x) { return cospi(x); }
 __device__ inline float d_sinpi(float x) { return sinpif(x); }
@@ -68,9 +80,16 @@ __device__ inline float over_rc(float r, double r_c) {
 }
 __device__ inline double over_rc(double r, double r_c) { return r * (1.0 / r_c); }
 
-// A_lambda(u) with u = s d, and optionally dA_lambda/dd (= s * dA/du).
-template <int L, typename R, bool GRAD>
-__device__ inline void angular(R ux, R uy, R uz, R s, R *A, R (*dA)[3]) {
+// v times a constant that every edge shares: in FP32 the constant as a sum of two floats, since its
+// rounding would be the same for every edge.
+__device__ inline float times_const(float v, double k) {
+    const float hi = (float)k, lo = (float)(k - (double)hi);
+    return fmaf(v, hi, v * lo);
+}
+__device__ inline double times_const(double v, double k) { return v * k; }
+
+// A_lambda(u) with u = s d.
+template <int L, typename R> __device__ inline void angular(R ux, R uy, R uz, R *A) {
     constexpr LamTab<L> T{};
     constexpr int N = LamTab<L>::N;
     R px[L + 1], py[L + 1], pz[L + 1];
@@ -82,15 +101,7 @@ __device__ inline void angular(R ux, R uy, R uz, R s, R *A, R (*dA)[3]) {
         pz[k] = pz[k - 1] * uz;
     }
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const int lx = T.lx[k], ly = T.ly[k], lz = T.lz[k];
-        A[k] = px[lx] * py[ly] * pz[lz];
-        if constexpr (GRAD) {
-            dA[k][0] = lx ? s * R(lx) * px[lx > 0 ? lx - 1 : 0] * py[ly] * pz[lz] : R(0);
-            dA[k][1] = ly ? s * R(ly) * px[lx] * py[ly > 0 ? ly - 1 : 0] * pz[lz] : R(0);
-            dA[k][2] = lz ? s * R(lz) * px[lx] * py[ly] * pz[lz > 0 ? lz - 1 : 0] : R(0);
-        }
-    }
+    for (int k = 0; k < N; ++k) A[k] = px[T.lx[k]] * py[T.ly[k]] * pz[T.lz[k]];
 }
 
 // In-cutoff compaction of the (r_c + skin) list for the current positions: each row's
@@ -214,12 +225,11 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
     for (int l = 0; l < NL; ++l)
 #pragma unroll
         for (int u = 0; u < KG; ++u) acc[l][u] = R(0);
-    R cen[KG], alp[KG];
+    Radial<R> rad[KG];
 #pragma unroll
-    for (int u = 0; u < KG; ++u) { cen[u] = R(ec.centres[KG * q + u]); alp[u] = gauss_const<R>(ec, KG * q + u); }
+    for (int u = 0; u < KG; ++u) rad[u] = radial<R>(ec, KG * q + u);
     const double4 pi = a.p4[i];
     const double xi = pi.x, yi = pi.y, zi = pi.z;
-    const R s = R(ec.ang_scale);
     const int nl = cl.nloc[i], cnt = nl + cl.ngh[i], last = cnt - 1;
     const int64_t lo = cl.row[i], gb = cl.row[i + 1] - cl.ngh[i];
     auto slot = [&](int e) -> int64_t { return e < nl ? lo + e : gb + (e - nl); };
@@ -262,13 +272,12 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
         const R uc = R(0.5) * d_cospi(over_rc(r, ec.r_c)) + R(0.5);
         const R fc = live ? uc * uc : R(0);
         R A[NL];
-        angular<L, R, false>(R(ec.ang_scale * dx), R(ec.ang_scale * dy), R(ec.ang_scale * dz), s, A, nullptr);
+        angular<L, R>(R(ec.ang_scale * dx), R(ec.ang_scale * dy), R(ec.ang_scale * dz), A);
         // the quad's 4 edges into this lane's channels
         auto edge = [&](const R rs, const R fs, const R (&As)[NL], const R (&cs)[KG]) {
 #pragma unroll
             for (int u = 0; u < KG; ++u) {
-                const R xm = rs - cen[u];
-                const R w = cs[u] * gauss(alp[u], xm) * fs;
+                const R w = cs[u] * gauss(rad[u], rs - rad[u].c) * fs;
 #pragma unroll
                 for (int l = 0; l < NL; ++l) acc[l][u] += w * As[l];
             }
@@ -307,7 +316,7 @@ __global__ __launch_bounds__(256) void k_edge_fwd(EdgeArgs a, CutList cl, EdgeCo
 // Per-edge radial/cutoff factors shared by both adjoint roles.
 template <int K, typename R> struct EdgeGeo {
     R r, ex, ey, ez, fc, dfc;
-    R Rm[K], dRm[K];
+    R Rm[K];
 };
 
 template <int K, typename R>
@@ -318,14 +327,12 @@ __device__ inline void edge_geo(const EdgeConsts &ec, double dx, double dy, doub
     const R t = over_rc(g.r, ec.r_c);
     const R u = R(0.5) * d_cospi(t) + R(0.5);
     g.fc = u * u;
-    g.dfc = -u * R(M_PI / ec.r_c) * d_sinpi(t);
+    g.dfc = -times_const(u * d_sinpi(t), M_PI / ec.r_c);
     g.ex = R(dx) * rinv; g.ey = R(dy) * rinv; g.ez = R(dz) * rinv;
 #pragma unroll
     for (int m = 0; m < K; ++m) {
-        const R xm = g.r - R(ec.centres[m]);
-        const R al = R(ec.alphas[m]);
-        g.Rm[m] = gauss(gauss_const<R>(ec, m), xm);
-        g.dRm[m] = R(-2) * al * xm * g.Rm[m];
+        const Radial<R> q = radial<R>(ec, m);
+        g.Rm[m] = gauss(q, g.r - q.c);
     }
 }
 
@@ -408,7 +415,6 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
     if (x < a.n) {
         const double4 pi = a.p4[x];
         const double xi = pi.x, yi = pi.y, zi = pi.z;
-        const R s = R(ec.ang_scale);
         const R *sb = sS[grp];
         const int nl = cl.nloc[x], cnt = nl + cl.ngh[x];
         const int64_t lo = cl.row[x], gb = cl.row[x + 1] - cl.ngh[x];
@@ -474,19 +480,23 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
                     P += w * u[m];
                     cacc[m] += w * Al;
                 }
-                if (lx) gx += P * (s * R(lx) * px[lx > 0 ? lx - 1 : 0] * py[ly] * pz[lz]);
-                if (ly) gy += P * (s * R(ly) * px[lx] * py[ly > 0 ? ly - 1 : 0] * pz[lz]);
-                if (lz) gz += P * (s * R(lz) * px[lx] * py[ly] * pz[lz > 0 ? lz - 1 : 0]);
+                // dA/du; the factor s of dA/dd is applied once, below
+                if (lx) gx += P * (R(lx) * px[lx > 0 ? lx - 1 : 0] * py[ly] * pz[lz]);
+                if (ly) gy += P * (R(ly) * px[lx] * py[ly > 0 ? ly - 1 : 0] * pz[lz]);
+                if (lz) gz += P * (R(lz) * px[lx] * py[ly] * pz[lz > 0 ? lz - 1 : 0]);
             }
-            // c_m dR_m/dr = -2 alpha_m (r - r_m) u_m, formed here rather than kept through the loop
+            // c_m dR_m/dr = gauss_slope u_m, formed here rather than kept through the loop
             R sAP = R(0), sAQ = R(0);
 #pragma unroll
             for (int m = 0; m < K; ++m) {
                 sAP += cacc[m] * u[m];
-                sAQ += cacc[m] * (R(-2) * R(ec.alphas[m]) * (g.r - R(ec.centres[m])) * u[m]);
+                const Radial<R> q = radial<R>(ec, m);
+                sAQ += cacc[m] * (gauss_slope(q, g.r - q.c) * u[m]);
             }
+            sAQ = times_const(sAQ, kSlopeUnit<R>);
             const R rad = g.dfc * sAP + g.fc * sAQ;
-            gx = g.fc * gx + rad * g.ex; gy = g.fc * gy + rad * g.ey; gz = g.fc * gz + rad * g.ez;
+            const R fs = times_const(g.fc, ec.ang_scale);
+            gx = fs * gx + rad * g.ex; gy = fs * gy + rad * g.ey; gz = fs * gz + rad * g.ez;
             f0 += gx; f1 += gy; f2 += gz;
             R *out = rec + f * RS;
             st4(out, gx, gy, gz, R(0));

@@ -9,7 +9,9 @@ namespace reann {
 struct EdgeConsts {
     double centres[16];
     double alphas[16];
-    double alphas2[16];   // alphas * log2(e): the FP32 kernels evaluate exp(-a x^2) as 2^(-a2 x^2)
+    // FP32 kernels: exp(-alpha (r - c)^2) as 2^(-a (r - c)^2) with a = alpha log2(e); the centre is
+    // c32 + its rounding, which enters as b32 = 2 a (centre - c32)
+    float c32[16], a32[16], b32[16];
     double r_c;
     double rc2;       // r_c^2 in FP64: in-cutoff test of a list entry
     double ang_scale;

@@ -148,7 +148,10 @@ EdgeConsts Model::edge_consts() const {
     for (int m = 0; m < K; ++m) {
         e.centres[m] = centres[m];
         e.alphas[m] = alphas[m];
-        e.alphas2[m] = alphas[m] * 1.4426950408889634;   // log2(e)
+        const double a2 = alphas[m] * 1.4426950408889634;   // log2(e)
+        e.c32[m] = (float)centres[m];
+        e.a32[m] = (float)a2;
+        e.b32[m] = (float)(2.0 * a2 * (centres[m] - (double)e.c32[m]));
     }
     e.r_c = r_c;
     e.rc2 = r_c * r_c;
