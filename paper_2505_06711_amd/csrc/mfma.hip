@@ -475,24 +475,6 @@ __device__ inline void fused_layer(const typename Fuse<OP>::T *X, int ldx, const
 
 }  // namespace
 
-// Multinomial weight l! / (lx! ly! lz!) of Cartesian component q (components by order, then lx, ly
-// descending).
-constexpr float lambda_weight(int L, int q) {
-    int k = 0;
-    for (int l = 0; l <= L; ++l)
-        for (int x = l; x >= 0; --x)
-            for (int y = l - x; y >= 0; --y, ++k)
-                if (k == q) {
-                    int w = 1;
-                    for (int j = 2; j <= l; ++j) w *= j;
-                    for (int j = 2; j <= x; ++j) w /= j;
-                    for (int j = 2; j <= y; ++j) w /= j;
-                    for (int j = 2; j <= l - x - y; ++j) w /= j;
-                    return (float)w;
-                }
-    return 0.0f;
-}
-
 // Density features of order l of tile row r for the pairs (a, b >= a) with a in [A0, A1):
 // X[r][l P + idx(a, b)] = sum over the components q of order l of w_q S[q][a] S[q][b].
 // A tile row past the segment's end takes the segment's last row (its results are never
@@ -532,10 +514,6 @@ constexpr int pair_split(int K, int num, int den) {
     while (den * n < num * (K * (K + 1) / 2)) n += K - A++;
     return A;
 }
-
-// Features of the NN input (L = 0: the radial form's K sums), and their chunks.
-constexpr int fused_features(int L, int K) { return L == 0 ? K : n_feat(L, K); }
-constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Forward of one element's NN over rows [0, rows): C = out_layer(SiLU(... SiLU(rho W_0^T + b_0) ...))
 // with rho the density of S.  H (the hidden width) and (L, K) are compile-time constants.

@@ -8,7 +8,7 @@
 
 namespace reann {
 
-enum class OpType { F32 = 0, BF16 = 1, FP8 = 2 };
+enum class OpType { F32 = 0, BF16 = 1, FP8 = 2, F64 = 3 };   // F64: the packed operands of the FP64 NN only
 
 constexpr int kMfmaKC = 32;   // K chunk staged per iteration; weight rows are padded to it
 
@@ -40,6 +40,28 @@ inline size_t packed_elems(OpType op, int rows, int cols) {
 void pack_operand(hipStream_t st, OpType op, const float *src, int rows, int cols, int ld_src, void *dst,
                   const float *scale);
 
+// Multinomial weight l! / (lx! ly! lz!) of Cartesian component q (components by order, then lx, ly
+// descending).
+constexpr float lambda_weight(int L, int q) {
+    int k = 0;
+    for (int l = 0; l <= L; ++l)
+        for (int x = l; x >= 0; --x)
+            for (int y = l - x; y >= 0; --y, ++k)
+                if (k == q) {
+                    int w = 1;
+                    for (int j = 2; j <= l; ++j) w *= j;
+                    for (int j = 2; j <= x; ++j) w /= j;
+                    for (int j = 2; j <= y; ++j) w /= j;
+                    for (int j = 2; j <= l - x - y; ++j) w /= j;
+                    return (float)w;
+                }
+    return 0.0f;
+}
+
+// Features of the NN input (L = 0: the radial form's K sums), and their chunks.
+constexpr int fused_features(int L, int K) { return L == 0 ? K : n_feat(L, K); }
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
 // Fused atomic NN (every layer of one element's NN in one launch, FP32 or BF16 operands).
 constexpr int kFuseBM = 32;      // rows per workgroup
 constexpr int kFuseSmallBM = 16; // rows per workgroup of a launch with few rows
@@ -49,17 +71,17 @@ constexpr int kFuseMaxNh = 4;    // hidden layers
 constexpr int kFuseMaxOut = 16;  // output width
 constexpr int kFuseMaxNLK = 160; // orbital sums per row (NL * K)
 
-struct FusedNN {
+template <typename R> struct FusedNNT {
     int64_t rows;                 // rows of this element's segment
     int F, H, nh, dout;           // input width, hidden width, hidden layers, output width
     int L, K;                     // angular order and radial channels of the density input
-    const float *S;               // orbital sums [rows][NL*K] (the NN input is their density)
+    const R *S;               // orbital sums [rows][NL*K] (the NN input is their density)
     // packed operands (pack_operand): forward, layer k [out][in]; adjoint, its transpose
     const void *W[kFuseMaxNh];
-    const float *b[kFuseMaxNh];   // forward: hidden-layer biases
-    float *Z[kFuseMaxNh];         // pre-activations [rows][H]: written by forward, read by adjoint
-    const float *Wout, *bout;     // output layer [dout][H], [dout] (FP32)
-    const double *Wout64, *bout64;   // forward with dout = 1 (the energy NN): the same in FP64
+    const R *b[kFuseMaxNh];       // forward: hidden-layer biases
+    R *Z[kFuseMaxNh];             // pre-activations [rows][H]: written by forward, read by adjoint
+    const R *Wout, *bout;         // output layer [dout][H], [dout]
+    const double *Wout64, *bout64;   // FP32 data, forward with dout = 1 (the energy NN): the same in FP64
     // FP8 forward only (1 / 1 / NULL otherwise): layer k's product is multiplied by zscale[k]
     // before its bias; the input of hidden layer k >= 1 is stored as h * hinv[k]; the layer-0
     // input (the density) as rho_f * xinv[f] (the calibrated per-feature scales, whose inverses
@@ -72,30 +94,33 @@ struct FusedNN {
     // to the copies' rows of Cg.  Adjoint: the copies' rows of Gg are added to G, in that order.
     const int2 *copy_rng;
     const int32_t *copy_idx;
-    float *Cg;
-    const float *Gg;
+    R *Cg;
+    const R *Gg;
     // Radial form's residual (NULL otherwise), [rows][K].  Forward: resid is added to the outputs.
     // Adjoint: next_in is added to G (after the copies), and the sum is kept in next_out.
-    const float *resid;
-    const float *next_in;
-    float *next_out;
+    const R *resid;
+    const R *next_in;
+    R *next_out;
     // Adjoint of the energy NN (dout = 1), which takes no G: row r's output adjoint is
     // seed_scale g w[perm[r]] (g = *seed_g or 1; w = seed_w in caller order or 1)
     double seed_scale;
     const double *seed_g, *seed_w;
     const int32_t *perm;
-    const float *G;               // adjoint of a message NN: output adjoint [rows][K]
-    float *C;                     // forward: outputs [rows][dout]; adjoint: dE/dS [rows][NL*K]
+    const R *G;                   // adjoint of a message NN: output adjoint [rows][K]
+    R *C;                         // forward: outputs [rows][dout]; adjoint: dE/dS [rows][NL*K]
 };
+using FusedNN = FusedNNT<float>;
+using FusedNN64 = FusedNNT<double>;
 
 // Segments of the same NN shape (the elements' rows of one layer, or locals and ghosts) for
 // one launch of the fused kernels.  Kernel arguments stay well under 4 KiB.
 constexpr int kFuseMaxSeg = 4;
-struct FusedMulti {
+template <typename R> struct FusedMultiT {
     int n;
     int64_t tile0[kFuseMaxSeg + 1];   // first block of each segment; tile0[n] = total blocks
-    FusedNN seg[kFuseMaxSeg];
+    FusedNNT<R> seg[kFuseMaxSeg];
 };
+using FusedMulti = FusedMultiT<float>;
 static_assert(sizeof(FusedMulti) < 3072, "kernel arguments");
 
 // Whether the fused kernels take these shapes (every operand type: FP8 runs the forward only,
@@ -112,6 +137,15 @@ void silu_absmax(hipStream_t st, int64_t rows, int H, int ld, const float *Z, fl
 // adjoint to dE/dS) over nseg segments of one NN shape, kFuseMaxSeg to a launch; returns the
 // launches.
 int mlp_fused_segments(hipStream_t st, OpType op, bool fwd, const FusedNN *segs, int nseg);
+
+// The same in FP64 (data, operands and accumulation): whether its kernels take a model, its operands
+// (element (r, c) of a matrix at src[r ld_row + c ld_col]; for K chunk kc of 8 and block j of 16
+// rows, lane l holds the pair k = 8 kc + 2 (l / 16) .. of row 16 j + l % 16 at ((kc nblk + j) 64 + l) 2,
+// zero past the matrix), and the launches.
+bool fused64_ok(int L, int K, int F, int H, int nh);
+size_t packed64_elems(int rows, int cols);
+void pack_operand64(hipStream_t st, const double *src, int rows, int cols, int ld_row, int ld_col, double *dst);
+int mlp64_segments(hipStream_t st, bool fwd, const FusedNN64 *segs, int nseg);
 
 inline size_t op_bytes(OpType op) { return op == OpType::F32 ? 4 : (op == OpType::BF16 ? 2 : 1); }
 

@@ -75,6 +75,30 @@ const MfmaSet &Model::mfma(int device, hipStream_t st, bool energy, OpType op) {
     const NNLayout &lay = energy ? en_nn : msg_nn;
     const std::vector<double> &blob = energy ? en : msg;
     const int count = energy ? n_species : (T_max - 1) * n_species;
+    if (op == OpType::F64) {   // packed from the FP64 weights on the device
+        size_t bytes = 0;
+        for (int q = 0; q < count; ++q)
+            for (int k = 0; k < nh; ++k) {
+                set->off_fwd.push_back(bytes);
+                bytes += packed64_elems(lay.dout[k], lay.din[k]) * 8;
+                set->off_bwd.push_back(bytes);
+                bytes += packed64_elems(lay.din[k], lay.dout[k]) * 8;
+            }
+        if (count > 0) {
+            set->buf.ensure(bytes);
+            const double *src = energy ? w.en64.as<double>() : w.msg64.as<double>();
+            for (int q = 0; q < count; ++q)
+                for (int k = 0; k < nh; ++k) {
+                    const double *W = src + (size_t)q * lay.size + lay.w_off[k];
+                    const int dout = lay.dout[k], din = lay.din[k];
+                    pack_operand64(st, W, dout, din, din, 1, (double *)(set->buf.as<char>() + set->off_fwd[q * nh + k]));
+                    pack_operand64(st, W, din, dout, 1, din, (double *)(set->buf.as<char>() + set->off_bwd[q * nh + k]));
+                }
+            HIP_OK(hipStreamSynchronize(st));
+        }
+        slot = std::move(set);
+        return *slot;
+    }
     // host: padded FP32 copies of every matrix, then one device conversion per matrix
     std::vector<float> host;
     std::vector<size_t> foff;          // float offset of each padded matrix in `host`
@@ -141,6 +165,12 @@ bool Model::on_device(int device, int prec) {
     if (prec == REANN_FP8)   // the FP8 rung also calibrates in FP32 and runs its adjoint in BF16
         return has(OpType::FP8) && has(OpType::F32) && has(OpType::BF16);
     return has(prec == REANN_BF16 ? OpType::BF16 : OpType::F32);
+}
+
+bool Model::has_packed64(int device) {
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = dev.find(device);
+    return it != dev.end() && it->second->mf[0][(int)OpType::F64] && it->second->mf[1][(int)OpType::F64];
 }
 
 EdgeConsts Model::edge_consts() const {
@@ -219,7 +249,11 @@ void Plan::init(Ctx *c_, Model *mm, const int32_t *spec, int64_t nn, const doubl
     HIP_OK(hipMemcpyAsync(ds, species.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_OK(hipStreamSynchronize(st));
     m->weights(ctx->device, st);
-    if (!fp64) {
+    fused64 = fp64 && m->fused64_form() && (!current_arena() || m->has_packed64(ctx->device));
+    if (fp64) {
+        if (fused64)
+            for (bool e : {false, true}) m->mfma(ctx->device, st, e, OpType::F64);
+    } else {
         m->mfma(ctx->device, st, false, op);
         m->mfma(ctx->device, st, true, op);
         if (op == OpType::FP8)   // calibration forward in FP32, adjoint in BF16
@@ -291,13 +325,12 @@ int64_t Plan::collect_timing(double *ms, int64_t *nlaunch) {
     return steps;
 }
 
-// whether both atomic NNs run as fused kernels (FP32, BF16 or FP8 operands)
-bool Plan::fused() const { return !fp64 && m->fused_form(); }
-
 bool Model::fused_form() const {
     // the fused kernels form the paired density (or, at L = 0, take the radial form's sums)
     return form != REANN_FORM_DIAG && fused_nn_ok(F, H, nh, K, NL * K) && fused_nn_ok(F, H, nh, 1, NL * K);
 }
+
+bool Model::fused64_form() const { return fused_form() && fused64_ok(L, K, F, H, nh); }
 
 void Plan::alloc_buffers() {
     const int K = m->K, NL = m->NL, F = m->F, H = m->H, nh = m->nh;
@@ -374,14 +407,132 @@ int Plan::nn_ranges(int s, bool energy, int64_t (&a)[2], int64_t (&rows)[2]) con
     return 2;
 }
 
+// The NN of layer t (the energy NN if `energy`) on the fused kernels: one launch over all elements'
+// rows (and ghosts'), which are independent; returns the launches.
+template <typename R> int Plan::fused_forward(hipStream_t st, int t, bool energy) {
+    DeviceWeights &w = m->weights(ctx->device, st);
+    const NNLayout &lay = energy ? m->en_nn : m->msg_nn;
+    const char *blob = energy ? (fp64 ? w.en64.as<char>() : w.en32.as<char>())
+                              : (fp64 ? w.msg64.as<char>() : w.msg32.as<char>());
+    const int F = m->F, H = m->H, nh = m->nh, K = m->K, dout = energy ? 1 : K;
+    const bool f8 = fp8_fused();
+    const MfmaSet *mf = f8 ? fp8set[energy ? 1 : 0].get() : &m->mfma(ctx->device, st, energy, fp64 ? OpType::F64 : op);
+    std::vector<FusedNNT<R>> segs;
+    for (int s = 0; s < m->n_species; ++s) {
+        int64_t ra[2], rn[2];
+        const int nr = nn_ranges(s, energy, ra, rn);
+        for (int q = 0; q < nr; ++q) {
+            const int64_t a = ra[q], rows = rn[q];
+            if (rows <= 0) continue;
+            const int64_t nn_index = energy ? s : (int64_t)t * m->n_species + s;
+            const char *p = blob + (size_t)nn_index * lay.size * rs;
+            char *out = energy ? y.as<char>() + (size_t)a * rs : cptr(t + 1) + (size_t)a * K * rs;
+            FusedNNT<R> f{};
+            f.rows = rows; f.F = F; f.H = H; f.nh = nh; f.dout = dout;
+            f.L = m->L; f.K = K;
+            f.S = (const R *)(Sptr(t) + (size_t)a * m->NL * K * rs);
+            for (int k = 0; k < nh; ++k) {
+                const size_t qi = (size_t)nn_index * nh + k;
+                f.W[k] = mf->buf.as<char>() + mf->off_fwd[qi];
+                f.b[k] = (const R *)(p + lay.b_off[k] * rs);
+                f.Z[k] = (R *)(Zptr(t, k) + (size_t)a * H * rs);
+                f.zscale[k] = f8 ? fp8_zscale[energy ? 1 : 0][qi] : 1.0f;
+                f.hinv[k] = f8 ? fp8_hinv[energy ? 1 : 0][qi] : 1.0f;
+            }
+            f.xinv = f8 ? fp8_xinv[energy ? 1 : 0].as<float>() + (size_t)nn_index * F : nullptr;
+            f.Wout = (const R *)(p + lay.w_off[nh] * rs);
+            f.bout = (const R *)(p + lay.b_off[nh] * rs);
+            if (energy) {   // the energy readout takes its weights and bias in FP64
+                const double *p64 = w.en64.as<double>() + (size_t)nn_index * lay.size;
+                f.Wout64 = p64 + lay.w_off[nh];
+                f.bout64 = p64 + lay.b_off[nh];
+            }
+            f.C = (R *)out;
+            if (!energy) {
+                if (!nodefeat) {   // the ghosts receive their owners' messages from the launch
+                    f.copy_rng = nl.copy_rng.ptr() + a;
+                    f.copy_idx = nl.copy_idx.ptr();
+                    f.Cg = (R *)(cptr(t + 1) + (size_t)n * K * rs);
+                }
+                if (radial()) f.resid = (const R *)(cptr(t) + (size_t)a * K * rs);   // c^{t+1} = c^t + NN(x^t)
+            }
+            segs.push_back(f);
+        }
+    }
+    if (segs.empty()) return 0;
+    if constexpr (sizeof(R) == 8) return mlp64_segments(st, true, segs.data(), (int)segs.size());
+    else return mlp_fused_segments(st, op, true, segs.data(), (int)segs.size());
+}
+
+// Its VJP, from output adjoint gout [n][ldg] (the energy NN forms its own from d_g) to Sbar, the
+// density adjoint included; a message NN adds the ghosts' message adjoints and the radial form's
+// residual adjoint to gout.
+template <typename R>
+int Plan::fused_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g) {
+    DeviceWeights &w = m->weights(ctx->device, st);
+    const NNLayout &lay = energy ? m->en_nn : m->msg_nn;
+    const char *blob = energy ? (fp64 ? w.en64.as<char>() : w.en32.as<char>())
+                              : (fp64 ? w.msg64.as<char>() : w.msg32.as<char>());
+    const int F = m->F, H = m->H, nh = m->nh;
+    // the FP8 rung's adjoint takes BF16 operands (the forward's FP8 scales are calibrated for
+    // activations, not for their adjoints)
+    const OpType bop = fp8_fused() ? OpType::BF16 : (fp64 ? OpType::F64 : op);
+    const MfmaSet *mf = &m->mfma(ctx->device, st, energy, bop);
+    std::vector<FusedNNT<R>> segs;
+    for (int s = 0; s < m->n_species; ++s) {
+        int64_t ra[2], rn[2];
+        const int nr = nn_ranges(s, energy, ra, rn);
+        for (int q = 0; q < nr; ++q) {
+            const int64_t a = ra[q], rows = rn[q];
+            if (rows <= 0) continue;
+            const int64_t nn_index = energy ? s : (int64_t)t * m->n_species + s;
+            const char *p = blob + (size_t)nn_index * lay.size * rs;
+            const char *gin = gout + (size_t)a * ldg * rs;
+            FusedNNT<R> f{};
+            f.rows = rows; f.F = F; f.H = H; f.nh = nh; f.dout = lay.dout[nh];
+            f.L = m->L; f.K = m->K;
+            f.S = (const R *)(Sptr(t) + (size_t)a * m->NL * m->K * rs);
+            for (int k = 0; k < nh; ++k) {
+                const size_t qi = (size_t)nn_index * nh + k;
+                f.W[k] = mf->buf.as<char>() + mf->off_bwd[qi];
+                f.Z[k] = (R *)(Zptr(t, k) + (size_t)a * H * rs);
+            }
+            f.Wout = (const R *)(p + lay.w_off[nh] * rs);
+            if (energy) {
+                f.seed_scale = m->energy_scale;
+                f.seed_g = d_g;
+                f.seed_w = have_ew ? d_ew.ptr() : nullptr;
+                f.perm = nl.perm.ptr() + a;
+            } else {
+                const int K = m->K;
+                f.G = (const R *)gin;
+                if (!nodefeat) {
+                    f.copy_rng = nl.copy_rng.ptr() + a;
+                    f.copy_idx = nl.copy_idx.ptr();
+                    f.Gg = (const R *)(gout + (size_t)n * K * rs);
+                }
+                if (radial()) {   // t is the layer of the NN: c^{t+1} reaches E through c^{t+2} too
+                    R *next = (R *)(cbar_next.as<char>() + (size_t)a * K * rs);
+                    f.next_in = t + 1 < T - 1 ? next : nullptr;
+                    f.next_out = t > 0 ? next : nullptr;
+                }
+            }
+            f.C = (R *)(Sbar.as<char>() + (size_t)a * m->NL * m->K * rs);
+            segs.push_back(f);
+        }
+    }
+    if (segs.empty()) return 0;
+    if constexpr (sizeof(R) == 8) return mlp64_segments(st, false, segs.data(), (int)segs.size());
+    else return mlp_fused_segments(st, bop, false, segs.data(), (int)segs.size());
+}
+
 int Plan::nn_forward(hipStream_t st, int t, bool energy) {
+    if (fused()) return fp64 ? fused_forward<double>(st, t, energy) : fused_forward<float>(st, t, energy);
     DeviceWeights &w = m->weights(ctx->device, st);
     const NNLayout &lay = energy ? m->en_nn : m->msg_nn;
     const char *blob = energy ? (fp64 ? w.en64.as<char>() : w.en32.as<char>())
                               : (fp64 ? w.msg64.as<char>() : w.msg32.as<char>());
     const int F = m->F, H = m->H, nh = m->nh, K = m->K;
-    int nfused = 0;
-    std::vector<FusedNN> segs;   // the fused kernel's segments, launched together below
     for (int s = 0; s < m->n_species; ++s) {
       int64_t ra[2], rn[2];
       const int nr = nn_ranges(s, energy, ra, rn);
@@ -392,43 +543,9 @@ int Plan::nn_forward(hipStream_t st, int t, bool energy) {
         const char *p = blob + (size_t)nn_index * lay.size * rs;
         const char *A = featptr(t) + (size_t)a * F * rs;
         int lda = F;
-        const bool f8 = fp8_fused();
-        const MfmaSet *mf = fp64 ? nullptr : (f8 ? fp8set[energy ? 1 : 0].get() : &m->mfma(ctx->device, st, energy, op));
+        const MfmaSet *mf = fp64 ? nullptr : &m->mfma(ctx->device, st, energy, op);
         char *out = energy ? y.as<char>() + (size_t)a * rs : cptr(t + 1) + (size_t)a * K * rs;
         const int dout = energy ? 1 : K;
-        if (fused()) {
-            FusedNN f{};
-            f.rows = rows; f.F = F; f.H = H; f.nh = nh; f.dout = dout;
-            f.L = m->L; f.K = K;
-            f.S = (const float *)(Sptr(t) + (size_t)a * m->NL * K * rs);
-            for (int k = 0; k < nh; ++k) {
-                const size_t qi = (size_t)nn_index * nh + k;
-                f.W[k] = mf->buf.as<char>() + mf->off_fwd[qi];
-                f.b[k] = (const float *)(p + lay.b_off[k] * rs);
-                f.Z[k] = (float *)(Zptr(t, k) + (size_t)a * H * rs);
-                f.zscale[k] = f8 ? fp8_zscale[energy ? 1 : 0][qi] : 1.0f;
-                f.hinv[k] = f8 ? fp8_hinv[energy ? 1 : 0][qi] : 1.0f;
-            }
-            f.xinv = f8 ? fp8_xinv[energy ? 1 : 0].as<float>() + (size_t)nn_index * F : nullptr;
-            f.Wout = (const float *)(p + lay.w_off[nh] * rs);
-            f.bout = (const float *)(p + lay.b_off[nh] * rs);
-            if (energy) {   // the energy readout takes its weights and bias in FP64
-                const double *p64 = w.en64.as<double>() + (size_t)nn_index * lay.size;
-                f.Wout64 = p64 + lay.w_off[nh];
-                f.bout64 = p64 + lay.b_off[nh];
-            }
-            f.C = (float *)out;
-            if (!energy) {
-                if (!nodefeat) {   // the ghosts receive their owners' messages from the launch
-                    f.copy_rng = nl.copy_rng.ptr() + a;
-                    f.copy_idx = nl.copy_idx.ptr();
-                    f.Cg = (float *)(cptr(t + 1) + (size_t)n * K * rs);
-                }
-                if (radial()) f.resid = (const float *)(cptr(t) + (size_t)a * K * rs);   // c^{t+1} = c^t + NN(x^t)
-            }
-            segs.push_back(f);
-            continue;
-        }
         for (int k = 0; k < nh; ++k) {
             char *Zk = Zptr(t, k) + (size_t)a * H * rs;
             char *Hk = Hptr(t, k) + (size_t)a * H * rs;
@@ -458,24 +575,19 @@ int Plan::nn_forward(hipStream_t st, int t, bool energy) {
                           (const float *)(p + lay.b_off[nh] * rs), (float *)out, dout);
       }
     }
-    // the elements' rows (and ghosts') are independent: one launch over all of them
-    if (!segs.empty()) nfused += mlp_fused_segments(st, op, true, segs.data(), (int)segs.size());
-    return nfused;
+    return 0;
 }
 
 // VJP of the NN applied at layer t (energy NN if `energy`), from output adjoint gout
-// [n][ldg] to Sbar when the NN is fused (the density adjoint included), else to rhobar.  The
-// fused kernel forms the energy NN's output adjoint itself (from d_g) and, for a message NN,
-// adds the ghosts' message adjoints and the radial form's residual adjoint to gout.
+// [n][ldg] to Sbar when the NN is fused (the density adjoint included), else to rhobar.
 int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g) {
+    if (fused())
+        return fp64 ? fused_vjp<double>(st, t, energy, gout, ldg, d_g) : fused_vjp<float>(st, t, energy, gout, ldg, d_g);
     DeviceWeights &w = m->weights(ctx->device, st);
     const NNLayout &lay = energy ? m->en_nn : m->msg_nn;
     const char *blob = energy ? (fp64 ? w.en64.as<char>() : w.en32.as<char>())
                               : (fp64 ? w.msg64.as<char>() : w.msg32.as<char>());
     const int F = m->F, H = m->H, nh = m->nh;
-    int nfused = 0;
-    std::vector<FusedNN> segs;   // the fused kernel's segments, launched together below
-    OpType seg_op = op;
     for (int s = 0; s < m->n_species; ++s) {
       int64_t ra[2], rn[2];
       const int nr = nn_ranges(s, energy, ra, rn);
@@ -489,45 +601,7 @@ int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, 
         int ldin = ldg;
         char *bufs[2] = {gA.as<char>(), gB.as<char>()};
         int cur = 0;
-        // the FP8 rung's adjoint takes BF16 operands (the forward's FP8 scales are calibrated
-        // for activations, not for their adjoints)
-        const OpType bop = fp8_fused() ? OpType::BF16 : op;
-        const MfmaSet *mf = fp64 ? nullptr : &m->mfma(ctx->device, st, energy, bop);
-        if (fused()) {
-            FusedNN f{};
-            f.rows = rows; f.F = F; f.H = H; f.nh = nh; f.dout = lay.dout[nh];
-            f.L = m->L; f.K = m->K;
-            f.S = (const float *)(Sptr(t) + (size_t)a * m->NL * m->K * rs);
-            for (int k = 0; k < nh; ++k) {
-                const size_t qi = (size_t)nn_index * nh + k;
-                f.W[k] = mf->buf.as<char>() + mf->off_bwd[qi];
-                f.Z[k] = (float *)(Zptr(t, k) + (size_t)a * H * rs);
-            }
-            f.Wout = (const float *)(p + lay.w_off[nh] * rs);
-            if (energy) {
-                f.seed_scale = m->energy_scale;
-                f.seed_g = d_g;
-                f.seed_w = have_ew ? d_ew.ptr() : nullptr;
-                f.perm = nl.perm.ptr() + a;
-            } else {
-                const int K = m->K;
-                f.G = (const float *)gin;
-                if (!nodefeat) {
-                    f.copy_rng = nl.copy_rng.ptr() + a;
-                    f.copy_idx = nl.copy_idx.ptr();
-                    f.Gg = (const float *)(gout + (size_t)n * K * rs);
-                }
-                if (radial()) {   // t is the layer of the NN: c^{t+1} reaches E through c^{t+2} too
-                    float *next = (float *)(cbar_next.as<char>() + (size_t)a * K * rs);
-                    f.next_in = t + 1 < T - 1 ? next : nullptr;
-                    f.next_out = t > 0 ? next : nullptr;
-                }
-            }
-            f.C = (float *)(Sbar.as<char>() + (size_t)a * m->NL * m->K * rs);
-            segs.push_back(f);
-            seg_op = bop;
-            continue;
-        }
+        const MfmaSet *mf = fp64 ? nullptr : &m->mfma(ctx->device, st, energy, op);
         for (int k = nh; k >= 1; --k) {
             char *dst = bufs[cur] + (size_t)a * H * rs;
             const char *Zk = Zptr(t, k - 1) + (size_t)a * H * rs;
@@ -564,8 +638,7 @@ int Plan::nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, 
         }
       }
     }
-    if (!segs.empty()) nfused += mlp_fused_segments(st, seg_op, false, segs.data(), (int)segs.size());
-    return nfused;
+    return 0;
 }
 
 bool Plan::prepare(const double *d_pos, hipStream_t st) {

@@ -38,7 +38,7 @@ struct MfmaSet {
 
 struct DeviceWeights {
     DevBuf msg64, en64, c064, msg32, en32, c032;
-    std::unique_ptr<MfmaSet> mf[2][3];      // [msg, energy][OpType]
+    std::unique_ptr<MfmaSet> mf[2][4];      // [msg, energy][OpType]
 };
 
 // A number no other model of this process has had: a freed model's address can be reused
@@ -64,6 +64,9 @@ struct Model {
     const MfmaSet &mfma(int device, hipStream_t st, bool energy, OpType op);
     // whether the atomic NNs run on the fused kernels (their operands are then packed)
     bool fused_form() const;
+    // whether they do in FP64, and whether the packed FP64 operands are on `device`
+    bool fused64_form() const;
+    bool has_packed64(int device);
     // whether the device copies an evaluation at `prec` reads already exist on `device`
     bool on_device(int device, int prec);
     EdgeConsts edge_consts() const;
@@ -196,7 +199,13 @@ struct Plan {
     // row ranges (first row, count) an NN of element s runs over: its locals, and for the
     // message NNs under node-feature exchange its ghosts too
     int nn_ranges(int s, bool energy, int64_t (&a)[2], int64_t (&rows)[2]) const;
-    bool fused() const;
+    bool fused() const { return fp64 ? fused64 : m->fused_form(); }
+    // the FP64 NN kernels: decided when the plan is made.  Inside the static scratch of an allocation-free
+    // evaluation the operands cannot be packed; if no plan has done that before, the layers run
+    // one by one.
+    bool fused64 = false;
+    template <typename R> int fused_forward(hipStream_t st, int t, bool energy);
+    template <typename R> int fused_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g);
     // both return the launches of the fused NN kernel (0 on the per-layer path)
     int nn_forward(hipStream_t st, int t, bool energy);
     int nn_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g);
