@@ -360,6 +360,9 @@ constexpr int kRowsPerBlock = 8;   // 256 threads = 8 half-waves, one row each
 // adds +g to F_k and the symmetric part of -d (x) g to the virial; the edge's record gets g
 // and (CBAR) the terms
 //   f_c R_m sum_lambda Sbar_k[lambda][m] A_lambda(d)  of  cbar_j[m].
+// Bound: vector instructions (495 per edge at L = 2, K = 12, 240 of them the two contractions: 119 of
+// the 143 us that 100,800 Cu atoms take without message terms), and with message terms the record
+// stores as well (503 MB there).
 // LPR lanes share a row and take its edges in turn; Sbar_k is staged in LDS and
 // read by all of them.  Each lane runs a two-stage pipeline: the list entry of its edge after
 // next and the position and message of its next edge are loaded while the current edge is
@@ -387,7 +390,16 @@ template <int LPR, typename R> __device__ inline R row_sum(R v) {
     return v;
 }
 
-template <int L, int K, typename R, bool CBAR, int LPR>
+typedef float fl4v __attribute__((ext_vector_type(4)));
+
+// Record buffers (of list slots) from this size on are written past the caches (STREAM): they do not
+// stay there until the gather reads them, and displace the messages and positions the edges share.
+// us at T = 3 (two centre passes and their gathers), cached / streamed stores: Cu atoms 32,000 (203 MB
+// of slots) 261 / 274, 42,592 (271 MB) 341 / 355, 62,500 (397 MB) 513 / 495, 100,800 821 / 804; water
+// atoms 65,856 (222 MB) 340 / 347, 98,304 (332 MB) 515 / 503, 192,000 985 / 941, 648,000 3,358 / 3,148.
+constexpr int64_t kStreamBytes = 300ll << 20;
+
+template <int L, int K, typename R, bool CBAR, int LPR, bool STREAM>
 __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(EdgeArgs a, CutList cl, EdgeConsts ec, const R *__restrict__ c,
                                                     const R *__restrict__ Sbar, R *__restrict__ F,
                                                     double *__restrict__ Wpart, R *__restrict__ rec, int first) {
@@ -396,6 +408,9 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
     constexpr LamTab<L> LT{};
     __shared__ R sS[kCentreRows][NL * K];
     __shared__ double sW[kCentreRows][9];
+    constexpr int RP = RS * (int)sizeof(R) / 16;   // 16-byte parts of a record
+    constexpr int RQ = RP | 1;   // odd: parts of neighbouring lanes fall into different banks
+    __shared__ float4 sR[CBAR && sizeof(R) == 4 ? 256 * RQ : 1];
     const int grp = threadIdx.x / LPR, lane = threadIdx.x % LPR;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t row0 = tile * kCentreRows;   // one row per LPR lanes
@@ -427,20 +442,22 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
         double xc = 0.0, yc = 0.0, zc = 0.0;
         R cc[K];
         int32_t jn = 0;
-        if (e < cnt) {
-            const int64_t s0 = slot(e), s1 = slot(min(e + LPR, last));
+        if (cnt > 0) {
+            const int64_t s0 = slot(min(e, last)), s1 = slot(min(e + LPR, last));
             const int32_t j0 = cl.col[s0];
             jn = cl.col[s1];
             { const double4 q = a.p4[j0]; xc = q.x; yc = q.y; zc = q.z; }
 #pragma unroll
             for (int m = 0; m < K; ++m) cc[m] = c[(int64_t)j0 * K + m];
         }
-        for (; e < cnt; e += LPR) {
+        // all of the row's lanes take part in every pass (see the stores); past the row's end they
+        // evaluate its last edge and drop it
+        for (int e0 = 0; e0 < cnt; e0 += LPR, e += LPR) {
+            const bool live = e < cnt;
             // keep Sbar_k in LDS: without this the compiler hoists the NL*K reads out of the
             // loop into registers, which caps occupancy
             asm volatile("" ::: "memory");
             const double dx = xc - xi, dy = yc - yi, dz = zc - zi;
-            const int64_t f = slot(e);
             EdgeGeo<K, R> g;
             edge_geo<K, R>(ec, dx, dy, dz, g);
             R u[K], cacc[K];
@@ -496,15 +513,47 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(Edge
             sAQ = times_const(sAQ, kSlopeUnit<R>);
             const R rad = g.dfc * sAP + g.fc * sAQ;
             const R fs = times_const(g.fc, ec.ang_scale);
-            gx = fs * gx + rad * g.ex; gy = fs * gy + rad * g.ey; gz = fs * gz + rad * g.ez;
+            gx = live ? fs * gx + rad * g.ex : R(0);
+            gy = live ? fs * gy + rad * g.ey : R(0);
+            gz = live ? fs * gz + rad * g.ez : R(0);
             f0 += gx; f1 += gy; f2 += gz;
-            R *out = rec + f * RS;
-            st4(out, gx, gy, gz, R(0));
-            if constexpr (CBAR) {
+            if constexpr (!CBAR || sizeof(R) == 8) {
+                if (live) {
+                    R *out = rec + slot(e) * RS;
+                    st4(out, gx, gy, gz, R(0));
+                    if constexpr (CBAR) {
+#pragma unroll
+                        for (int m = 0; m < K; m += 4)
+                            st4(out + 4 + m, g.fc * g.Rm[m] * cacc[m], g.fc * g.Rm[m + 1] * cacc[m + 1],
+                                g.fc * g.Rm[m + 2] * cacc[m + 2], g.fc * g.Rm[m + 3] * cacc[m + 3]);
+                    }
+                }
+            } else {
+                // The row's records of this pass are contiguous (but where its ghosts begin): they go
+                // through LDS so that a store's lanes write adjacent parts (each lane storing its own
+                // record as 16-byte parts, a request each: 258 us for 100,800 Cu atoms, 221 so)
+                R *mine = reinterpret_cast<R *>(sR + threadIdx.x * RQ);
+                st4(mine, gx, gy, gz, R(0));
 #pragma unroll
                 for (int m = 0; m < K; m += 4)
-                    st4(out + 4 + m, g.fc * g.Rm[m] * cacc[m], g.fc * g.Rm[m + 1] * cacc[m + 1],
+                    st4(mine + 4 + m, g.fc * g.Rm[m] * cacc[m], g.fc * g.Rm[m + 1] * cacc[m + 1],
                         g.fc * g.Rm[m + 2] * cacc[m + 2], g.fc * g.Rm[m + 3] * cacc[m + 3]);
+                // a wave's LDS accesses are done in order; the compiler is to keep them so
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
+                const float4 *row = sR + (threadIdx.x - lane) * RQ;
+#pragma unroll
+                for (int q = 0; q < RP; ++q) {
+                    const int part = q * LPR + lane, er = e0 + part / RP;
+                    const float4 v = row[part / RP * RQ + part % RP];
+                    if (er < cnt) {
+                        fl4v *out = reinterpret_cast<fl4v *>(rec + slot(er) * RS) + part % RP;
+                        if constexpr (STREAM) __builtin_nontemporal_store(fl4v{v.x, v.y, v.z, v.w}, out);
+                        else *out = fl4v{v.x, v.y, v.z, v.w};
+                    }
+                }
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
             }
             const R ddx = R(dx), ddy = R(dy), ddz = R(dz);
             W[0] -= ddx * gx;
@@ -560,36 +609,38 @@ __global__ __launch_bounds__(256) void k_adj_gather(EdgeArgs a, CutList cl, cons
     R acc[4] = {R(0), R(0), R(0), R(0)};
     const int cnt = cl.nloc[x], last = cnt - 1;
     const int64_t lo = cl.row[x];
-    // U passes at a time, so that each lane has U independent (reverse slot -> record) loads
-    // in flight; indices past the row's end are clamped to its last edge and their records
-    // are not added
-    constexpr int U = 8;
+    // U passes at a time, so that each lane has U independent record loads in flight; indices past
+    // the row's end are clamped to its last edge and their records are not added.  The reverse slots
+    // of those edges are found with a lane per edge and handed out by permutes: with the edge's 4
+    // lanes each loading it, the address unit was busy half the time (100,800 Cu atoms, first gather
+    // 235 us, 221 so; U = 4, 8, 12: 239, 226, 221).
+    constexpr int U = CBAR ? 12 : 4, NI = U * EPP / 32;
     const int pc = part < NP ? 4 * part : 0;
-    for (int e0 = eg; e0 < cnt; e0 += U * EPP) {
-        int32_t rv[U];
+    for (int b = 0; b < cnt; b += U * EPP) {
+        int32_t idx[NI];
         if constexpr (MAKE) {
             // first gather of a step: the reverse compacted slot from the list slot, its
             // reverse and that one's compacted slot, kept in rslot for the later gathers
 #pragma unroll
-            for (int u = 0; u < U; ++u) rv[u] = cl.fslot[lo + min(e0 + u * EPP, last)];
+            for (int h = 0; h < NI; ++h) idx[h] = cl.fslot[lo + min(b + 32 * h + lane, last)];
 #pragma unroll
-            for (int u = 0; u < U; ++u) rv[u] = cl.rev[rv[u]];
+            for (int h = 0; h < NI; ++h) idx[h] = cl.rev[idx[h]];
 #pragma unroll
-            for (int u = 0; u < U; ++u) rv[u] = cl.cpos[rv[u]];
-            if (part == 0) {
+            for (int h = 0; h < NI; ++h) idx[h] = cl.cpos[idx[h]];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (e0 + u * EPP < cnt) cl.rslot[lo + e0 + u * EPP] = rv[u];
-            }
+            for (int h = 0; h < NI; ++h)
+                if (b + 32 * h + lane < cnt) cl.rslot[lo + b + 32 * h + lane] = idx[h];
         } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u) rv[u] = cl.rslot[lo + min(e0 + u * EPP, last)];
+            for (int h = 0; h < NI; ++h) idx[h] = cl.rslot[lo + min(b + 32 * h + lane, last)];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            const int e = u * EPP + eg;
+            const int32_t rv = CBAR ? __shfl(idx[u * EPP / 32], e & 31, 32) : idx[u];
             R v[4] = {R(0), R(0), R(0), R(0)};
-            add4(rec + (int64_t)rv[u] * RS + pc, v);
-            if (e0 + u * EPP < cnt && part < NP) {
+            add4(rec + (int64_t)rv * RS + pc, v);
+            if (b + e < cnt && part < NP) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[q] += v[q];
             }
@@ -658,13 +709,15 @@ int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs 
                         double *Wpart, void *rec) {
     const int nbc = edge_backward_blocks(a.n);
     const int lanes = centre_lanes(a.n);
-#define CEN_L(LL, KK, R, CB, LP)                                                                                  \
-    hipLaunchKernelGGL((k_adj_centre<LL, KK, R, CB, LP>), dim3(nbc), dim3(256), 0, st, a, cl, ec, (const R *)c, \
+    const bool stream = a.n_pairs * (int64_t)(edge_record_elems(K) * sizeof(float)) > kStreamBytes;
+#define CEN_L(LL, KK, R, CB, LP, STR)                                                                                  \
+    hipLaunchKernelGGL((k_adj_centre<LL, KK, R, CB, LP, STR>), dim3(nbc), dim3(256), 0, st, a, cl, ec, (const R *)c, \
                        (const R *)Sbar, (R *)F, Wpart, (R *)rec, first ? 1 : 0);
 #define CEN_T(LL, KK, R, CB)                                    \
-    if (lanes == 64) { CEN_L(LL, KK, R, CB, 64) }               \
-    else if (lanes == 32) { CEN_L(LL, KK, R, CB, 32) }          \
-    else { CEN_L(LL, KK, R, CB, 16) }
+    if (lanes == 64) { CEN_L(LL, KK, R, CB, 64, false) }               \
+    else if (lanes == 32) { CEN_L(LL, KK, R, CB, 32, false) }          \
+    else if (CB && sizeof(R) == 4 && stream) { CEN_L(LL, KK, R, CB, 16, (CB && sizeof(R) == 4)) } \
+    else { CEN_L(LL, KK, R, CB, 16, false) }
 #define CEN(LL, KK)                                             \
     if (fp64) {                                                 \
         if (want_cbar) { CEN_T(LL, KK, double, true) }          \

@@ -22,6 +22,7 @@ struct EdgeArgs {
     const int64_t *row;
     const int32_t *col;
     const double4 *p4;   // ext positions (x, y, z, 0)
+    int64_t n_pairs;     // list entries
 };
 
 // In-cutoff entries of the list for the current positions (same slot ranges as the list):

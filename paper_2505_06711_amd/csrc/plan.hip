@@ -801,7 +801,7 @@ void Plan::launch_forward(const double *d_pos, double *d_energy, double *d_atom_
         init_messages(st, fp64, nl.n_ext, K, nl.spec_ext.ptr(), fp64 ? w.c064.p : w.c032.p, cptr(0));
         c0_build = rebuilds;
     }
-    EdgeArgs ea{n, nl.n_ext, nl.row.ptr(), nl.col.ptr(), p4.as<double4>()};
+    EdgeArgs ea{n, nl.n_ext, nl.row.ptr(), nl.col.ptr(), p4.as<double4>(), nl.n_pairs};
     CutList cl = cutlist();
     compact_cutoff(st, ea, m->r_c, cl, word, check ? check_host.get_double() : nullptr);
     if (check) HIP_OK(hipEventRecord(check_ev, st));
@@ -849,7 +849,7 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
     if (!have_forward) fail(REANN_E_STATE, "backward called before forward");
     TraceRange range("reann: backward");
     const int K = m->K;
-    EdgeArgs ea{n, nl.n_ext, nl.row.ptr(), nl.col.ptr(), p4.as<double4>()};
+    EdgeArgs ea{n, nl.n_ext, nl.row.ptr(), nl.col.ptr(), p4.as<double4>(), nl.n_pairs};
     const CutList cl = cutlist();
     const EdgeConsts ec = m->edge_consts();
     const DensityConsts dc = m->density_consts();
