@@ -162,19 +162,23 @@ __global__ __launch_bounds__(kKeBlock) void k_ke_final(int64_t n, int nb, double
 }
 
 // A system of up to kKeOneBlock / 3 atoms: the kick, the kinetic energy and the thermostat in
-// one block (thread t takes components t, t + kKeBlock, ... in order, then the tree).
-constexpr int64_t kKeOneBlock = 3 * 8192;
+// one block (thread t takes components t, t + kKeOne, ... in order, then the tree).  Its time is that of a
+// thread's loads in series: over a mix of systems of 100 to 8,000 atoms 21.4 us on average with 256
+// threads, 9.8 with 1,024.  Larger systems take k_vv_kick_ke and k_ke_final, 5.3 + 4.6 us (1,024
+// to 8,000 atoms: 15.6 us in one block).
+constexpr int64_t kKeOneBlock = 3 * 2048;
+constexpr int kKeOne = 1024;
 
-__global__ __launch_bounds__(kKeBlock) void k_vv_kick_ke_one(int64_t n3, double dt, const int32_t *__restrict__ spec,
+__global__ __launch_bounds__(kKeOne) void k_vv_kick_ke_one(int64_t n3, double dt, const int32_t *__restrict__ spec,
                                                               const double *__restrict__ minv, double *__restrict__ v,
                                                               const double *__restrict__ Fold, const double *__restrict__ F,
                                                               unsigned long long *__restrict__ dmax, double T0, double tau,
                                                               int kind, const double *__restrict__ rng,
                                                               double *__restrict__ aux, double *__restrict__ head) {
-    __shared__ double sh[3][kKeBlock];
+    __shared__ double sh[3][kKeOne];
     if (threadIdx.x == 0) dmax[0] = dmax[3] = 0ull;
     double s = 0.0, vm = 0.0, am = 0.0;
-    for (int64_t t = threadIdx.x; t < n3; t += kKeBlock) {
+    for (int64_t t = threadIdx.x; t < n3; t += kKeOne) {
         const double mi = minv[spec[t / 3]];
         const double vt = v[t] + 0.5 * (Fold[t] + F[t]) * mi * kAccel * dt;
         v[t] = vt;
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(kKeBlock) void k_vv_kick_ke_one(int64_t n3, double 
     }
     sh[0][threadIdx.x] = s; sh[1][threadIdx.x] = vm; sh[2][threadIdx.x] = am;
     __syncthreads();
-    for (int h = kKeBlock / 2; h > 0; h >>= 1) {
+    for (int h = kKeOne / 2; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h) {
             sh[0][threadIdx.x] += sh[0][threadIdx.x + h];
             sh[1][threadIdx.x] = fmax(sh[1][threadIdx.x], sh[1][threadIdx.x + h]);
@@ -596,7 +600,7 @@ void reann_server::enqueue_tail(hipStream_t st, Sys &sy, bool vv, double dt, int
     // dt (head[14]), raised by k_vv_post as integer maxima
     unsigned long long *dmax = reinterpret_cast<unsigned long long *>(sy.d_out.as<double>() + 11);
     if (vv && n3 <= kKeOneBlock) {
-        hipLaunchKernelGGL(k_vv_kick_ke_one, dim3(1), dim3(kKeBlock), 0, st, n3, dt, sy.d_spec.ptr(), d_minv.as<double>(),
+        hipLaunchKernelGGL(k_vv_kick_ke_one, dim3(1), dim3(kKeOne), 0, st, n3, dt, sy.d_spec.ptr(), d_minv.as<double>(),
                            sy.d_vel.as<double>(), sy.d_Fold.as<double>(), sy.F(), dmax, opt.thermostat_K,
                            opt.thermostat_tau_fs, (int)opt.thermostat, sy.d_rng.as<double>(), sy.d_aux.as<double>(),
                            sy.KE());
