@@ -342,7 +342,7 @@ void Plan::alloc_buffers() {
     if (!fused() && !radial()) rho.ensure((size_t)T * ns * F * rs);
     Z.ensure((size_t)T * nh * ns * H * rs);
     if (!fused()) Hh.ensure((size_t)2 * ns * H * rs);
-    y.ensure((size_t)n * K * rs);
+    y.ensure((size_t)n * rs);   // the energy NN's outputs
     if (!fused()) ybar.ensure((size_t)n * rs);
     Eat.ensure((size_t)n * 8);
     Epart.ensure((size_t)(grid_for(n, 256) + 1) * 8);
