@@ -361,7 +361,7 @@ constexpr int kRowsPerBlock = 8;   // 256 threads = 8 half-waves, one row each
 // and (CBAR) the terms
 //   f_c R_m sum_lambda Sbar_k[lambda][m] A_lambda(d)  of  cbar_j[m].
 // Bound: vector instructions (495 per edge at L = 2, K = 12, 240 of them the two contractions: 119 of
-// the 143 us that 100,800 Cu atoms take without message terms), and with message terms the record
+// the 137 us that 100,800 Cu atoms take without message terms), and with message terms the record
 // stores as well (503 MB there).
 // LPR lanes share a row and take its edges in turn; Sbar_k is staged in LDS and
 // read by all of them.  Each lane runs a two-stage pipeline: the list entry of its edge after
@@ -371,9 +371,9 @@ constexpr int kRowsPerBlock = 8;   // 256 threads = 8 half-waves, one row each
 // with CBAR, 4 without).
 // 16 lanes leave about 5 edges in series per lane and waste few slots; a launch of few rows does
 // not fill the chip with them and waits for that series, so it takes more lanes per row.  us per
-// launch with message terms, 16 / 32 / 64 lanes: 192 water atoms 9.4 / 7.7 / 5.8, 1,372 Cu atoms 16.8 /
-// 12.8 / 11.2, 4,000 18.9 / 16.5 / 19.4, 8,232 water atoms 15.8 / 16.2 / 17.8, 20,520 28.3 / 30.6 / 37.4
-// (FP64: 256 Cu atoms 22.5 / 16.1 / 12.9, 3,000 water atoms 15.6 / 14.9 / 15.4, 6,864 Cu 51 / 63 / 80).
+// launch with message terms, 16 / 32 / 64 lanes: 192 water atoms 8.0 / 6.7 / 6.3, 1,372 Cu atoms 15.1 /
+// 12.0 / 10.2, 4,000 16.3 / 13.2 / 16.7, 8,232 water atoms 15.2 / 16.6 / 18.9, 20,520 27.6 / 30.1 / 38.2
+// (FP64: 256 Cu atoms 19.2 / 14.3 / 11.0, 3,000 water atoms 15.3 / 15.2 / 15.6, 6,912 Cu 46 / 57 / 72).
 static int centre_lanes(int64_t n) { return n <= 1536 ? 64 : (n <= 4096 ? 32 : 16); }
 
 // Sum over the LPR lanes of a row (all active): the quad sums, then each lane adds the mirrored
@@ -399,8 +399,14 @@ typedef float fl4v __attribute__((ext_vector_type(4)));
 // atoms 65,856 (222 MB) 340 / 347, 98,304 (332 MB) 515 / 503, 192,000 985 / 941, 648,000 3,358 / 3,148.
 constexpr int64_t kStreamBytes = 300ll << 20;
 
+// Waves a SIMD that the registers are held to (FP32).  4 where that costs two registers or fewer: K = 8
+// with message terms 28 -> 26 us for 20,520 water atoms, 83 -> 75 for 65,856 and 845 -> 766 for 648,000;
+// K = 12 without 52 -> 48 us for 32,000 Cu atoms and 150 -> 137 for 100,800.  K = 12 with message
+// terms spills (64 -> 82 us for 32,000), and launches of few rows do not fill the chip.
+constexpr int centre_waves(int K, int LPR, bool CBAR) { return (K <= 8 || !CBAR) && LPR == 16 ? 4 : 3; }
+
 template <int L, int K, typename R, bool CBAR, int LPR, bool STREAM>
-__global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void k_adj_centre(EdgeArgs a, CutList cl, EdgeConsts ec, const R *__restrict__ c,
+__global__ __launch_bounds__(256, sizeof(R) == 4 ? centre_waves(K, LPR, CBAR) : 1) void k_adj_centre(EdgeArgs a, CutList cl, EdgeConsts ec, const R *__restrict__ c,
                                                     const R *__restrict__ Sbar, R *__restrict__ F,
                                                     double *__restrict__ Wpart, R *__restrict__ rec, int first) {
     constexpr int NL = n_lambda(L), kCentreRows = 256 / LPR;
