@@ -251,7 +251,10 @@ void reann_plan_free(reann_plan *p);
  *   reann_plan_update_list: the skin check at positions d_pos (device FP64 [n][3]) on
  *     hip_stream, and a rebuild when it fails or no list exists; synchronises that stream.
  *     rebuilt (host int32, may be NULL) is set to 1 after a rebuild, else 0.  A rebuild may
- *     move the plan's device buffers, so a graph captured before it must be captured again. */
+ *     move the plan's device buffers, so a graph captured before it must be captured again, and it
+ *     ends the state of the last forward (a backward needs another forward first).
+ * A rebuild that fails (positions refused, or no memory left), here or in a forward, leaves the
+ * plan without a list: the next forward or reann_plan_update_list builds one, or fails again. */
 reann_status reann_plan_set_list_policy(reann_plan *p, int32_t auto_check);
 reann_status reann_plan_update_list(reann_plan *p, const double *d_pos, void *hip_stream, int32_t *rebuilt);
 

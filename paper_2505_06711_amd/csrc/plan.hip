@@ -391,10 +391,15 @@ bool Plan::list_stale(const double *d_pos, hipStream_t st) {
 }
 
 void Plan::rebuild(const double *d_pos, hipStream_t st, bool defer_check) {
+    // A build that fails on the way leaves parts of the old list and parts of the new one (the wraps
+    // and the reference positions among the first written): until it is through, there is no list to
+    // measure the skin rule against and no forward to go back from, so that the next call builds
+    // again (and refuses the same positions again).
+    built = have_forward = false;
     build_nlist(st, d_pos, d_species.ptr(), n, m->n_species, g, m->r_c, skin, nl, ns, nodefeat, defer_check);
+    alloc_buffers();
     built = true;
     ++rebuilds;
-    alloc_buffers();
     if (fp8_fused() && !fp8_ready) calibrate_fp8(d_pos, st);
 }
 
