@@ -570,6 +570,10 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? centre_waves(K, LPR, CBAR) : 
             W[5] -= R(0.5) * (ddy * gz + ddz * gy);
         }
     }
+    // the block's virial so far in this sweep, for launches that keep it (requested ahead of the sums)
+    double wprev = 0.0;
+    if constexpr (LPR > 16)
+        if (threadIdx.x < 9 && !first) wprev = Wpart[tile * 9 + threadIdx.x];
     f0 = row_sum<LPR>(f0); f1 = row_sum<LPR>(f1); f2 = row_sum<LPR>(f2);
     double Wd[6];
 #pragma unroll
@@ -589,7 +593,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? centre_waves(K, LPR, CBAR) : 
     if (threadIdx.x < 9) {
         double t = 0.0;
         for (int h = 0; h < kCentreRows; ++h) t += sW[h][threadIdx.x];
-        Wpart[tile * 9 + threadIdx.x] = t;
+        Wpart[tile * 9 + threadIdx.x] = wprev + t;
     }
 }
 
@@ -708,13 +712,21 @@ void edge_forward(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, co
     LAUNCH_OK("k_edge_fwd");
 }
 
-int edge_backward_blocks(int64_t n) { return grid_for(n, 256 / centre_lanes(n)); }
+static int centre_blocks(int64_t n) { return grid_for(n, 256 / centre_lanes(n)); }
 
-int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
-                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, bool first, void *F,
+// A row per block and layer where a block takes 16 rows.  Blocks of 4 or 8 rows would make that up to
+// 18 bytes an atom and layer (at 16 layers 0.4 of 64 MiB of static scratch), so they add a layer's partials
+// to the row of the layers before: no slower there (3,000 atoms, T = 3: 39.3 us of centre launches either
+// way), while 1.2M atoms take 4,026 us so and 3,970 with a row for each layer.
+int edge_virial_rows(int64_t n, int T) { return centre_lanes(n) > 16 ? centre_blocks(n) : T * centre_blocks(n); }
+
+void edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
+                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, int layer, void *F,
                         double *Wpart, void *rec) {
-    const int nbc = edge_backward_blocks(a.n);
+    const int nbc = centre_blocks(a.n);
     const int lanes = centre_lanes(a.n);
+    const bool first = layer == 0;
+    if (lanes == 16) Wpart += (int64_t)layer * nbc * 9;
     const bool stream = a.n_pairs * (int64_t)(edge_record_elems(K) * sizeof(float)) > kStreamBytes;
 #define CEN_L(LL, KK, R, CB, LP, STR)                                                                                  \
     hipLaunchKernelGGL((k_adj_centre<LL, KK, R, CB, LP, STR>), dim3(nbc), dim3(256), 0, st, a, cl, ec, (const R *)c, \
@@ -737,7 +749,6 @@ int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs 
 #undef CEN_T
 #undef CEN_L
     LAUNCH_OK("k_adj_centre");
-    return nbc;
 }
 
 void edge_adjoint_gather(hipStream_t st, bool fp64, int K, const EdgeArgs &a, const CutList &cl, bool want_cbar,

@@ -53,20 +53,20 @@ void edge_forward(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, co
 // writes at the edge's compacted slot the record of what it gives the neighbour end.
 // Neighbour role (every ext row): sums the records of the row's incoming edges through
 // rslot.
-//   Sbar [n][NL][K] (locals), c [n_ext][K]; F [n_ext][3] is accumulated, or with `first` (the
-// sweep's first layer) set, by the centre role for the locals and by the gather for the ghosts;
-//   cbar [n_ext][K] is overwritten when want_cbar; Wpart receives one FP64 [9] per block
-// of the centre-role launch (the return value is that block count); rec holds
+//   Sbar [n][NL][K] (locals), c [n_ext][K]; layer counts the sweep's layers from 0 (the last one).
+// F [n_ext][3] is accumulated over them, and set by layer 0: by the centre role for the locals, by the
+// gather for the ghosts.  cbar [n_ext][K] is overwritten when want_cbar; Wpart holds
+// edge_virial_rows(n, T) rows of FP64 [9], whose sum is the virial; rec holds
 // edge_record_elems(K) working-type values per (compacted) list slot.
-int edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
-                        const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, bool first, void *F,
-                        double *Wpart, void *rec);
+void edge_adjoint_centre(hipStream_t st, bool fp64, int L, int K, const EdgeArgs &a, const CutList &cl,
+                         const EdgeConsts &ec, const void *c, const void *Sbar, bool want_cbar, int layer, void *F,
+                         double *Wpart, void *rec);
 // first: the first gather after compact_cutoff also fills rslot; later gathers read it.
 void edge_adjoint_gather(hipStream_t st, bool fp64, int K, const EdgeArgs &a, const CutList &cl, bool want_cbar,
                          bool first, const void *rec, void *F, void *cbar);
 // Values per edge record: the edge gradient (3, padded to 4) and K adjoint-message terms.
 inline int edge_record_elems(int K) { return 4 + K; }
-int edge_backward_blocks(int64_t n);   // blocks of the centre-role launch over n local rows
+int edge_virial_rows(int64_t n, int T);   // rows of virial partials of a sweep over n local rows
 
 // c[n + g][:] = c[owner[g]][:]
 void ghost_gather(hipStream_t st, bool fp64, int64_t n, int64_t n_gh, int K, const int32_t *owner, void *c);

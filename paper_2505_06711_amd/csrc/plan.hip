@@ -356,7 +356,8 @@ void Plan::alloc_buffers() {
     }
     cbar.ensure((size_t)ne * K * rs);
     this->F.ensure((size_t)ne * 3 * rs);
-    Wpart.ensure((size_t)(T * (edge_backward_blocks(n) + 1) + kVirialBlocks) * 9 * 8);   // per layer, summed once
+    const int nw = edge_virial_rows(n, T);
+    Wpart.ensure((size_t)(nw + (nw > kVirialRows ? kVirialBlocks : 0)) * 9 * 8);
     disp.ensure(1025 * 8);
     col2.ensure((size_t)(nl.n_pairs + 1) * 4);
     fslot.ensure((size_t)(nl.n_pairs + 1) * 4);
@@ -869,12 +870,9 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
         else density_vjp(st, fp64, m->L, K, n, dc, Sptr(T - 1), rhobar.p, Sbar.p);
         mark(st, PH_DENSITY_ADJ, 1);
     }
-    // the centre role's per-block virial partials of the T layers side by side, summed once
-    int nbw = 0;
     for (int t = T - 1; t >= 0; --t) {
-        const int nb = edge_adjoint_centre(st, fp64, m->L, K, ea, cl, ec, cptr(t), Sbar.p, t > 0, t == T - 1, this->F.p,
-                                           Wpart.as<double>() + (size_t)nbw * 9, erec.p);
-        nbw += nb;
+        edge_adjoint_centre(st, fp64, m->L, K, ea, cl, ec, cptr(t), Sbar.p, t > 0, T - 1 - t, this->F.p,
+                            Wpart.as<double>(), erec.p);
         mark(st, PH_ADJ_CENTRE, 1);
         edge_adjoint_gather(st, fp64, K, ea, cl, t > 0, t == T - 1, erec.p, this->F.p, cbar.p);
         mark(st, PH_ADJ_GATHER, 1);
@@ -908,7 +906,7 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
     // the seed carried g; forces are -dE/dx already scaled; the ghosts' forces go back to their
     // owners and the virial partials are summed in the same launch
     forces_out(st, fp64, n, this->F.p, nl.perm.ptr(), nl.copy_rng.ptr(), nl.copy_idx.ptr(), d_forces,
-               Wpart.as<double>(), nbw, d_virial);
+               Wpart.as<double>(), edge_virial_rows(n, T), d_virial);
     mark(st, PH_OTHER);
     if (timing) ++timed_steps;
 }
