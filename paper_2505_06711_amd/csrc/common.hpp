@@ -52,7 +52,7 @@ inline Arena *&current_arena() {
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
-    bool owned = true;   // false: memory of an Arena, not freed here
+    bool owned = true;   // false: memory of an Arena or part of another buffer, not freed here
     DevBuf() = default;
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;

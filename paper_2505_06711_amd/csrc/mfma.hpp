@@ -139,12 +139,15 @@ void silu_absmax(hipStream_t st, int64_t rows, int H, int ld, const float *Z, fl
 int mlp_fused_segments(hipStream_t st, OpType op, bool fwd, const FusedNN *segs, int nseg);
 
 // The same in FP64 (data, operands and accumulation): whether its kernels take a model, its operands
-// (element (r, c) of a matrix at src[r ld_row + c ld_col]; for K chunk kc of 8 and block j of 16
-// rows, lane l holds the pair k = 8 kc + 2 (l / 16) .. of row 16 j + l % 16 at ((kc nblk + j) 64 + l) 2,
-// zero past the matrix), and the launches.
+// (for K chunk kc of 8 and block j of 16 rows, lane l holds the pair k = 8 kc + 2 (l / 16) .. of row
+// 16 j + l % 16 at ((kc nblk + j) 64 + l) 2, zero past the matrix), and the launches.
 bool fused64_ok(int L, int K, int F, int H, int nh);
 size_t packed64_elems(int rows, int cols);
-void pack_operand64(hipStream_t st, const double *src, int rows, int cols, int ld_row, int ld_col, double *dst);
+// The matrices of one NN: element (r, c) at src + r ld_row + c ld_col of the NN's weights, its packed
+// form from dst of the NN's operands; the NNs are src_stride and dst_stride elements apart.
+struct Pack64Matrix { int rows, cols, ld_row, ld_col; int64_t src, dst; };
+struct Pack64 { int n; int64_t src_stride, dst_stride; Pack64Matrix m[2 * kFuseMaxNh]; };
+void pack_operands64(hipStream_t st, const Pack64 &pk, int count, const double *src, double *dst);
 int mlp64_segments(hipStream_t st, bool fwd, const FusedNN64 *segs, int nseg);
 
 inline size_t op_bytes(OpType op) { return op == OpType::F32 ? 4 : (op == OpType::BF16 ? 2 : 1); }

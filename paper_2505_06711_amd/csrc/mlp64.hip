@@ -7,7 +7,7 @@
 //   (weights); D[l / 16 + 4 r][l % 16] is register r
 // K advances in chunks of 8: a lane holds the pair k = 8 kc + 2 (l / 16) + {0, 1} of both operands
 // (one 16-byte load each) and feeds its two values to two instructions.  The weights are packed so
-// that a wave's fragment is one contiguous KB (pack_operand64).  The row stride of every LDS array is
+// that a wave's fragment is one contiguous KB (pack_operands64).  The row stride of every LDS array is
 // 4 banks mod 16 banks, odd multiples of 4: the 16 rows a fragment load touches fall into different
 // banks.
 //
@@ -289,14 +289,18 @@ template <int H, int L, int K> __global__ __launch_bounds__(4 * H) void k_mlp64_
     bwd64_body<H, L, K>(pm.seg[s], ((int64_t)blockIdx.x - pm.tile0[s]) * kBM64);
 }
 
-__global__ void k_pack64(const double *__restrict__ src, int rows, int cols, int ld_row, int ld_col,
-                         double *__restrict__ dst, int64_t count) {
+// block (x, matrix, NN)
+__global__ void k_pack64(Pack64 pk, const double *__restrict__ src, double *__restrict__ dst) {
+    const Pack64Matrix m = pk.m[blockIdx.y];
+    const int nblk = (m.rows + 15) / 16, nck = (m.cols + kKC64 - 1) / kKC64;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= count) return;
-    const int nblk = (rows + 15) / 16, e = (int)(t & 1), l = (int)(t >> 1 & 63);
+    if (t >= (int64_t)nblk * nck * 128) return;
+    const int e = (int)(t & 1), l = (int)(t >> 1 & 63);
     const int64_t frag = t >> 7;
     const int r = (int)(frag % nblk) * 16 + l % 16, c = (int)(frag / nblk) * kKC64 + 2 * (l / 16) + e;
-    dst[t] = r < rows && c < cols ? src[(int64_t)r * ld_row + (int64_t)c * ld_col] : 0.0;
+    const double *W = src + blockIdx.z * pk.src_stride + m.src;
+    dst[blockIdx.z * pk.dst_stride + m.dst + t] =
+        r < m.rows && c < m.cols ? W[(int64_t)r * m.ld_row + (int64_t)c * m.ld_col] : 0.0;
 }
 
 template <int H> bool launch_lk(hipStream_t st, bool fwd, unsigned tiles, const FusedMultiT<double> &pm) {
@@ -323,9 +327,10 @@ size_t packed64_elems(int rows, int cols) {
     return (size_t)((rows + 15) / 16 * 16) * (size_t)((cols + kKC64 - 1) / kKC64 * kKC64);
 }
 
-void pack_operand64(hipStream_t st, const double *src, int rows, int cols, int ld_row, int ld_col, double *dst) {
-    const int64_t count = (int64_t)packed64_elems(rows, cols);
-    hipLaunchKernelGGL(k_pack64, dim3(grid_for(count, 256)), dim3(256), 0, st, src, rows, cols, ld_row, ld_col, dst, count);
+void pack_operands64(hipStream_t st, const Pack64 &pk, int count, const double *src, double *dst) {
+    size_t most = 0;
+    for (int k = 0; k < pk.n; ++k) most = std::max(most, packed64_elems(pk.m[k].rows, pk.m[k].cols));
+    hipLaunchKernelGGL(k_pack64, dim3(grid_for(most, 256), pk.n, count), dim3(256), 0, st, pk, src, dst);
     LAUNCH_OK("k_pack64");
 }
 

@@ -50,13 +50,52 @@ static void upload(DevBuf &b, const std::vector<double> &v, bool to_float, hipSt
     }
 }
 
+// The FP64 weights of the message or energy NNs on the device and, where the FP64 kernels take them,
+// their packed operands, which lie behind them in the same allocation.
+std::unique_ptr<MfmaSet> Model::upload64(DevBuf &b, bool energy, hipStream_t st) const {
+    const std::vector<double> &v = energy ? en : msg;
+    if (!fused64_form()) {
+        upload(b, v, false, st);
+        return nullptr;
+    }
+    const NNLayout &lay = energy ? en_nn : msg_nn;
+    const int count = energy ? n_species : (T_max - 1) * n_species;
+    auto set = std::make_unique<MfmaSet>();
+    Pack64 pk{};
+    for (int k = 0; k < nh; ++k)
+        for (int dir = 0; dir < 2; ++dir) {   // W_k [dout][din] and its transpose
+            const int din = lay.din[k], dout = lay.dout[k];
+            Pack64Matrix &m = pk.m[pk.n++];
+            m = dir == 0 ? Pack64Matrix{dout, din, din, 1} : Pack64Matrix{din, dout, 1, din};
+            m.src = lay.w_off[k];
+            m.dst = pk.dst_stride;
+            pk.dst_stride += (int64_t)packed64_elems(m.rows, m.cols);
+        }
+    pk.src_stride = lay.size;
+    for (int q = 0; q < count; ++q)
+        for (int k = 0; k < nh; ++k) {
+            set->off_fwd.push_back((size_t)(q * pk.dst_stride + pk.m[2 * k].dst) * 8);
+            set->off_bwd.push_back((size_t)(q * pk.dst_stride + pk.m[2 * k + 1].dst) * 8);
+        }
+    const size_t off = (v.size() * 8 + 255) / 256 * 256, bytes = (size_t)count * pk.dst_stride * 8;
+    b.ensure(off + bytes);
+    upload(b, v, false, st);
+    if (count > 0) {
+        set->buf.p = b.as<char>() + off;
+        set->buf.bytes = bytes;
+        set->buf.owned = false;
+        pack_operands64(st, pk, count, b.as<double>(), set->buf.as<double>());
+    }
+    return set;
+}
+
 DeviceWeights &Model::weights(int device, hipStream_t st) {
     std::lock_guard<std::mutex> lk(mu);
     auto it = dev.find(device);
     if (it != dev.end()) return *it->second;
     auto w = std::make_unique<DeviceWeights>();
-    upload(w->msg64, msg, false, st);
-    upload(w->en64, en, false, st);
+    w->mf[0][(int)OpType::F64] = upload64(w->msg64, false, st);
+    w->mf[1][(int)OpType::F64] = upload64(w->en64, true, st);
     upload(w->c064, c0, false, st);
     upload(w->msg32, msg, true, st);
     upload(w->en32, en, true, st);
@@ -71,34 +110,11 @@ const MfmaSet &Model::mfma(int device, hipStream_t st, bool energy, OpType op) {
     std::lock_guard<std::mutex> lk(mu);
     auto &slot = w.mf[energy ? 1 : 0][(int)op];
     if (slot) return *slot;
+    if (op == OpType::F64) fail(REANN_E_DEVICE, "no packed FP64 operands");
     auto set = std::make_unique<MfmaSet>();
     const NNLayout &lay = energy ? en_nn : msg_nn;
     const std::vector<double> &blob = energy ? en : msg;
     const int count = energy ? n_species : (T_max - 1) * n_species;
-    if (op == OpType::F64) {   // packed from the FP64 weights on the device
-        size_t bytes = 0;
-        for (int q = 0; q < count; ++q)
-            for (int k = 0; k < nh; ++k) {
-                set->off_fwd.push_back(bytes);
-                bytes += packed64_elems(lay.dout[k], lay.din[k]) * 8;
-                set->off_bwd.push_back(bytes);
-                bytes += packed64_elems(lay.din[k], lay.dout[k]) * 8;
-            }
-        if (count > 0) {
-            set->buf.ensure(bytes);
-            const double *src = energy ? w.en64.as<double>() : w.msg64.as<double>();
-            for (int q = 0; q < count; ++q)
-                for (int k = 0; k < nh; ++k) {
-                    const double *W = src + (size_t)q * lay.size + lay.w_off[k];
-                    const int dout = lay.dout[k], din = lay.din[k];
-                    pack_operand64(st, W, dout, din, din, 1, (double *)(set->buf.as<char>() + set->off_fwd[q * nh + k]));
-                    pack_operand64(st, W, din, dout, 1, din, (double *)(set->buf.as<char>() + set->off_bwd[q * nh + k]));
-                }
-            HIP_OK(hipStreamSynchronize(st));
-        }
-        slot = std::move(set);
-        return *slot;
-    }
     // host: padded FP32 copies of every matrix, then one device conversion per matrix
     std::vector<float> host;
     std::vector<size_t> foff;          // float offset of each padded matrix in `host`
@@ -165,12 +181,6 @@ bool Model::on_device(int device, int prec) {
     if (prec == REANN_FP8)   // the FP8 rung also calibrates in FP32 and runs its adjoint in BF16
         return has(OpType::FP8) && has(OpType::F32) && has(OpType::BF16);
     return has(prec == REANN_BF16 ? OpType::BF16 : OpType::F32);
-}
-
-bool Model::has_packed64(int device) {
-    std::lock_guard<std::mutex> lk(mu);
-    auto it = dev.find(device);
-    return it != dev.end() && it->second->mf[0][(int)OpType::F64] && it->second->mf[1][(int)OpType::F64];
 }
 
 EdgeConsts Model::edge_consts() const {
@@ -249,11 +259,7 @@ void Plan::init(Ctx *c_, Model *mm, const int32_t *spec, int64_t nn, const doubl
     HIP_OK(hipMemcpyAsync(ds, species.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_OK(hipStreamSynchronize(st));
     m->weights(ctx->device, st);
-    fused64 = fp64 && m->fused64_form() && (!current_arena() || m->has_packed64(ctx->device));
-    if (fp64) {
-        if (fused64)
-            for (bool e : {false, true}) m->mfma(ctx->device, st, e, OpType::F64);
-    } else {
+    if (!fp64) {
         m->mfma(ctx->device, st, false, op);
         m->mfma(ctx->device, st, true, op);
         if (op == OpType::FP8)   // calibration forward in FP32, adjoint in BF16

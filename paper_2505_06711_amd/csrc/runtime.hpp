@@ -60,13 +60,14 @@ struct Model {
     std::map<int, std::unique_ptr<DeviceWeights>> dev;
     // device copy of the weights for `device` (created on first use)
     DeviceWeights &weights(int device, hipStream_t st);
-    // matrix-core operands of the message (energy = false) or energy NNs for `op`
+    // matrix-core operands of the message (energy = false) or energy NNs for `op` (F64: made with the
+    // weights, since an evaluation that may not allocate could not)
     const MfmaSet &mfma(int device, hipStream_t st, bool energy, OpType op);
     // whether the atomic NNs run on the fused kernels (their operands are then packed)
     bool fused_form() const;
-    // whether they do in FP64, and whether the packed FP64 operands are on `device`
+    // whether they do in FP64
     bool fused64_form() const;
-    bool has_packed64(int device);
+    std::unique_ptr<MfmaSet> upload64(DevBuf &b, bool energy, hipStream_t st) const;
     // whether the device copies an evaluation at `prec` reads already exist on `device`
     bool on_device(int device, int prec);
     EdgeConsts edge_consts() const;
@@ -199,11 +200,7 @@ struct Plan {
     // row ranges (first row, count) an NN of element s runs over: its locals, and for the
     // message NNs under node-feature exchange its ghosts too
     int nn_ranges(int s, bool energy, int64_t (&a)[2], int64_t (&rows)[2]) const;
-    bool fused() const { return fp64 ? fused64 : m->fused_form(); }
-    // the FP64 NN kernels: decided when the plan is made.  Inside the static scratch of an allocation-free
-    // evaluation the operands cannot be packed; if no plan has done that before, the layers run
-    // one by one.
-    bool fused64 = false;
+    bool fused() const { return fp64 ? m->fused64_form() : m->fused_form(); }
     template <typename R> int fused_forward(hipStream_t st, int t, bool energy);
     template <typename R> int fused_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g);
     // both return the launches of the fused NN kernel (0 on the per-layer path)

@@ -1011,9 +1011,6 @@ reann_status reann_server_create(const reann_model *m, const reann_server_opts *
             const OpType op = o->precision == REANN_BF16 ? OpType::BF16 : (o->precision == REANN_FP8 ? OpType::FP8 : OpType::F32);
             s->m->mfma(o->device, s->ctx.stream, false, op);
             s->m->mfma(o->device, s->ctx.stream, true, op);
-        } else if (s->m->fused64_form()) {
-            s->m->mfma(o->device, s->ctx.stream, false, OpType::F64);
-            s->m->mfma(o->device, s->ctx.stream, true, OpType::F64);
         }
         if (const char *ft = std::getenv("REANN_SERVER_FAULT_TICKET")) s->fault_ticket = std::atoll(ft);
         reann_server *raw = s.release();

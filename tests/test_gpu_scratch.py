@@ -1,7 +1,7 @@
 """The allocation-free evaluation near the size of its static scratch: open clusters that fit with
 every buffer at the size it needs (a few more atoms do not), at sixteen layers, where a row kept per
 layer and block costs the most.  Results against the allocating call, which shares the kernels: bit
-for bit."""
+for bit, whatever was evaluated before."""
 import numpy as np
 import pytest
 
@@ -33,3 +33,19 @@ def test_cluster_that_just_fits(rn, K, r_c, hidden, nh, precision, n):
     assert got[0] == want[0]
     np.testing.assert_array_equal(got[1], want[1])
     np.testing.assert_array_equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("form", ["reann", "radial"])
+def test_fp64_bits_do_not_depend_on_what_ran_before(rn, form):
+    """The FP64 evaluation that may not allocate, with only an FP32 call before it and after an FP64 one."""
+    m = (models.water_model if form == "reann" else models.water_model_radial)(T_max=3, seed=2)
+    s = systems.water_box(seed=2)
+    ctx, model = rn.Context(0), rn.Model(m)
+    rn.energy_forces(ctx, model, s, T=3, precision="fp32", skin=0.5)   # the model's device copies
+    first = rn.energy_forces(ctx, model, s, T=3, precision="fp64", skin=0.5, noalloc=True)
+    want = rn.energy_forces(ctx, model, s, T=3, precision="fp64", skin=0.5)
+    again = rn.energy_forces(ctx, model, s, T=3, precision="fp64", skin=0.5, noalloc=True)
+    for got in (first, again):
+        assert got[0] == want[0]
+        np.testing.assert_array_equal(got[1], want[1])
+        np.testing.assert_array_equal(got[2], want[2])
