@@ -461,7 +461,7 @@ template <typename R> int Plan::fused_forward(hipStream_t st, int t, bool energy
             }
             f.C = (R *)out;
             if (!energy) {
-                if (!nodefeat) {   // the ghosts receive their owners' messages from the launch
+                if (nn_copies()) {   // the ghosts receive their owners' messages from the launch
                     f.copy_rng = nl.copy_rng.ptr() + a;
                     f.copy_idx = nl.copy_idx.ptr();
                     f.Cg = (R *)(cptr(t + 1) + (size_t)n * K * rs);
@@ -843,7 +843,7 @@ void Plan::launch_forward(const double *d_pos, double *d_energy, double *d_atom_
                 add_into(st, fp64, nS() * K, cptr(t + 1), cptr(t));
                 mark(st, PH_OTHER);
             }
-            if (!nodefeat && !fused()) {
+            if (!nodefeat && !nn_copies()) {
                 ghost_gather(st, fp64, n, nl.n_gh, K, nl.gh_owner.ptr(), cptr(t + 1));
                 mark(st, PH_GHOST);
             }

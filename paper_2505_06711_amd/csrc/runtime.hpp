@@ -94,6 +94,13 @@ enum Phase {
 };
 static_assert(PH_OTHER + 1 == REANN_N_PHASES, "phase count");
 
+// Ghosts per atom up to which the launch of a fused message NN writes their messages too: a thread
+// writes its atom's copies one after another, which short periodic cells have many of; the gather
+// launch takes a thread for each.  us per FP32 forward at T = 3, in the launch / gathered: 108-atom
+// Cu cell (11 copies an atom) 74.0 / 77.1, 32 (24) 74.8 / 74.0, 4 (about 110) 86.3 / 73.2, one atom every
+// 1.8 A (over 500) 237 / 88; a wire of 12,000 (23) 252.8 / 243.5, slab of 14,400 (4) 199.6 / 198.3.
+constexpr int64_t kNNCopies = 16;
+
 struct Plan {
     Ctx *ctx = nullptr;
     Model *m = nullptr;
@@ -201,6 +208,8 @@ struct Plan {
     // message NNs under node-feature exchange its ghosts too
     int nn_ranges(int s, bool energy, int64_t (&a)[2], int64_t (&rows)[2]) const;
     bool fused() const { return fp64 ? m->fused64_form() : m->fused_form(); }
+    // whether the launch of a fused message NN writes the ghosts' messages too
+    bool nn_copies() const { return fused() && !nodefeat && nl.n_gh <= kNNCopies * n; }
     template <typename R> int fused_forward(hipStream_t st, int t, bool energy);
     template <typename R> int fused_vjp(hipStream_t st, int t, bool energy, const char *gout, int ldg, const double *d_g);
     // both return the launches of the fused NN kernel (0 on the per-layer path)
