@@ -324,10 +324,12 @@ __global__ void k_build_ext(Bins b, int64_t n, int64_t n_ext, const int32_t *__r
 //
 // Bound by load latency (few rows) and FP64 issue (many).  Before, rows whose keys held under 24
 // atoms on average took a thread each and the others a half-wave that walked its runs one bin at
-// a time.  Count + fill, before -> now: 3,000-atom water box (8,600 rows) 266 + 181 -> 14 + 19 us;
-// 100,800-atom crystal 318 + 177 -> 183 + 144 us; 1.2M-atom water split 2x2x2 (1.68M rows)
-// 1,724 + 1,525 -> 1,730 + 1,825 us, the fill now also clearing the reverse slots (a 0.42 GB
-// memset before).
+// a time.  Count + fill, before -> now: 3,000-atom water box (8,600 rows) 297 + 187 -> 15 + 20 us;
+// 100,800-atom crystal 305 + 161 -> 167 + 140 us; 1.2M-atom water split 2x2x2 (1.68M rows)
+// 1,715 + 1,471 -> 1,571 + 1,769 us, the fill now also clearing the reverse slots (a 0.42 GB
+// memset before).  Batches whose candidates end before the unrolled words do load no more (with 64
+// elements a batch has about 22): a rebuild of 400,000 atoms of 64 elements takes 5,930 us, 6,670 with
+// those loads and 6,190 with a thread a row; the 1.2M-atom box 5,920, 6,130 and 6,260.
 constexpr int kRowsPerBlk = 8;   // 256 threads, a half-wave per row
 constexpr int kRunSlots = 3;     // slots whose runs (9 each) are walked together
 constexpr int kRowUnroll = 4;    // words whose positions are loaded together
@@ -415,16 +417,18 @@ __global__ __launch_bounds__(256) void k_rows(Bins b, Geom g, int n_species, int
             double ex[kRowUnroll], ey[kRowUnroll], ez[kRowUnroll];
 #pragma unroll
             for (int u = 0; u < kRowUnroll; ++u) {
+                if (w0 + 32 * u >= total) break;   // uniform over the half-wave
                 const int c = w0 + 32 * u + lane;
                 e[u] = c < total ? atom(c) : (int)x;   // past the end: the atom itself, never a hit
             }
 #pragma unroll
             for (int u = 0; u < kRowUnroll; ++u) {
+                if (w0 + 32 * u >= total) break;
                 ex[u] = pext[e[u]]; ey[u] = pext[n_ext + e[u]]; ez[u] = pext[2 * n_ext + e[u]];
             }
 #pragma unroll
             for (int u = 0; u < kRowUnroll; ++u) {
-                if (w0 + 32 * u >= total) break;   // uniform over the half-wave
+                if (w0 + 32 * u >= total) break;
                 const double dx = ex[u] - xi, dy = ey[u] - yi, dz = ez[u] - zi;
                 const double dd2 = fma(dz, dz, fma(dy, dy, dx * dx));
                 const bool hit = e[u] != (int)x && dd2 < g.rc2;
