@@ -388,13 +388,11 @@ size_t Plan::device_bytes() const {
 
 bool Plan::list_stale(const double *d_pos, hipStream_t st) {
     if (!built) return true;
-    double d2 = 0;
     max_displacement2(st, nl, d_pos, disp.as<double>());
-    HIP_OK(hipMemcpyAsync(&d2, disp.p, 8, hipMemcpyDeviceToHost, st));
+    HIP_OK(hipMemcpyAsync(&moved2, disp.p, 8, hipMemcpyDeviceToHost, st));
     HIP_OK(hipStreamSynchronize(st));
     check_deferred();
-    const double half = 0.5 * skin;
-    return !(d2 <= half * half);
+    return !(moved2 <= 0.25 * skin * skin);
 }
 
 void Plan::rebuild(const double *d_pos, hipStream_t st, bool defer_check) {
@@ -787,9 +785,9 @@ void Plan::forward(const double *d_pos, double *d_energy, double *d_atom_energy,
         launch_forward(d_pos, d_energy, d_atom_energy, st, true);
         HIP_OK(hipEventSynchronize(check_ev));
         check_deferred();
-        const double half = 0.5 * skin;
-        if (*h <= half * half) return;
-        expect_stale = true;
+        moved2 = *h;
+        if (moved2 <= 0.25 * skin * skin) return;
+        expect_stale = moved_far();
         rebuild(d_pos, st);
         mark(st, PH_NLIST, 1);
         launch_forward(d_pos, d_energy, d_atom_energy, st);
@@ -797,7 +795,7 @@ void Plan::forward(const double *d_pos, double *d_energy, double *d_atom_energy,
     }
     const bool had_list = built;
     const bool rebuilt = auto_list ? prepare(d_pos, st) : false;
-    expect_stale = rebuilt && had_list;
+    expect_stale = rebuilt && had_list && moved_far();
     mark(st, PH_NLIST, rebuilt ? 1 : 0);
     launch_forward(d_pos, d_energy, d_atom_energy, st);
 }

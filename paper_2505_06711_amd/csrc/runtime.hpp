@@ -163,9 +163,14 @@ struct Plan {
     DevBuf check_word;
     PinnedWord check_host;
     hipEvent_t check_ev = nullptr;
-    // the last forward found its list stale: the next one (an unrelated frame, perhaps) asks first
-    // instead of running a forward on the old list beside the question
+    // the last forward found atoms further than skin from where its list was built, twice what the skin
+    // rule allows: an unrelated frame, and the next one is taken for another, so that it asks first
+    // instead of running a forward on the old list beside the question.  A trajectory passes the bound
+    // by one step's motion; asking first in the step after every rebuild took it 10-37 us longer (4,000
+    // Cu atoms, a rebuild every 3 / 10 / 30 steps: 295 / 225 / 204.5 us a step, 283 / 221 / 203 so).
     bool expect_stale = false;
+    double moved2 = 0.0;   // the squared displacement that the last skin check found
+    bool moved_far() const { return !(moved2 <= skin * skin); }
     // the two halves of prepare: the skin check alone (true if the list was never built or an
     // atom has moved more than skin/2 since), and the rebuild (with the FP8 calibration the
     // first time), which allocates
