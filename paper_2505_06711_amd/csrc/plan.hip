@@ -115,6 +115,8 @@ const MfmaSet &Model::mfma(int device, hipStream_t st, bool energy, OpType op) {
     const NNLayout &lay = energy ? en_nn : msg_nn;
     const std::vector<double> &blob = energy ? en : msg;
     const int count = energy ? n_species : (T_max - 1) * n_species;
+    // the fused kernels' operands are packed fragments, the per-layer kernel's are padded rows
+    const bool packed = fused_form();
     // host: padded FP32 copies of every matrix, then one device conversion per matrix
     std::vector<float> host;
     std::vector<size_t> foff;          // float offset of each padded matrix in `host`
@@ -138,8 +140,8 @@ const MfmaSet &Model::mfma(int device, hipStream_t st, bool energy, OpType op) {
                     }
                 scales.push_back(op == OpType::FP8 ? (amax > 0 ? (float)(amax / 448.0) : 1.0f) : 1.0f);
                 const int idx = (int)scales.size() - 1;
-                if (dir == 0) { set->sc_fwd.push_back(idx); set->ld_fwd.push_back(ld); }
-                else { set->sc_bwd.push_back(idx); set->ld_bwd.push_back(ld); }
+                (dir == 0 ? set->sc_fwd : set->sc_bwd).push_back(idx);
+                if (!packed) (dir == 0 ? set->ld_fwd : set->ld_bwd).push_back(ld);
             }
         }
     DevBuf tmp;
@@ -147,8 +149,6 @@ const MfmaSet &Model::mfma(int device, hipStream_t st, bool energy, OpType op) {
     if (!host.empty()) HIP_OK(hipMemcpyAsync(tmp.p, host.data(), host.size() * 4, hipMemcpyHostToDevice, st));
     set->scales.ensure(std::max<size_t>(scales.size(), 1) * 4);
     if (!scales.empty()) HIP_OK(hipMemcpyAsync(set->scales.p, scales.data(), scales.size() * 4, hipMemcpyHostToDevice, st));
-    // the fused kernels' operands are packed fragments, the per-layer kernel's are padded rows
-    const bool packed = fused_form();
     const size_t eb = op_bytes(op);
     std::vector<size_t> ooff(foff.size() + 1, 0);
     for (size_t i = 0; i < foff.size(); ++i) {
@@ -731,7 +731,6 @@ void Plan::calibrate_fp8(const double *d_pos, hipStream_t st) {
                 const double wsc = wmax > 0.0 ? wmax / 448.0 : 1.0;
                 scales.push_back((float)wsc);
                 set->off_fwd.push_back(0);
-                set->ld_fwd.push_back(ld);
                 fp8_zscale[e][(size_t)q * nh + k] = (float)(wsc * sig);
                 fp8_hinv[e][(size_t)q * nh + k] = (float)(1.0 / sig);
             }

@@ -32,7 +32,7 @@ NNLayout nn_layout(int F, int H, int nh, int out);
 struct MfmaSet {
     DevBuf buf, scales;
     std::vector<size_t> off_fwd, off_bwd;   // bytes, index q * nh + k
-    std::vector<int> ld_fwd, ld_bwd;
+    std::vector<int> ld_fwd, ld_bwd;        // padded rows only
     std::vector<int> sc_fwd, sc_bwd;        // index into scales
 };
 
