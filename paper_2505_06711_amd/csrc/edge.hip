@@ -12,8 +12,9 @@
 // and keeps +g_ij for F_i and the virial; what lands on j (-g_ij and the cbar_j terms) is
 // written as a record at the edge's compacted slot.  The neighbour-role kernel then gives
 // every ext row k the sum of the records of its edges j->k, found through a per-step map of
-// each entry to the compacted slot of its reverse.  Sums over a row's edges are taken across the lanes of a half-wave in a fixed
-// order, so results are deterministic.
+// each entry to the compacted slot of its reverse.  Sums over a row's edges are taken across the
+// lanes that share the row (4 or 16 in the forward, 16 to 64 in the centre role, 32 in the neighbour
+// role) in a fixed order, so results are deterministic.
 #include "edge.hpp"
 
 namespace reann {
@@ -187,7 +188,7 @@ __global__ void k_compact(EdgeArgs a, double rc2, int32_t *__restrict__ col2, in
 // loops still help until the padding of a row's last round of groups costs more (a row of 53
 // edges: 56 slots in one quad, 64 in four).  us per launch, 1 / 4 quads: 192 water atoms 14.7 / 6.0,
 // 20,520 24.3 / 17.8, 192,000 115.8 / 111.4, 1.2M 661 / 684; Cu 4,000 atoms 23.0 / 8.1, 100,800
-// 103.5 / 93.3; FP64 Cu 6,864 37.8 / 19.8.
+// 103.5 / 93.3, 202,464 181 / 171, 340,560 285 / 282, 389,344 322 / 323; FP64 Cu 6,864 37.8 / 19.8.
 constexpr int kFwdLanes = 4;
 constexpr int64_t kFwdQuadRows = 400000;   // rows up to which 4 quads share one
 
@@ -402,7 +403,8 @@ constexpr int64_t kStreamBytes = 300ll << 20;
 // Waves a SIMD that the registers are held to (FP32).  4 where that costs two registers or fewer: K = 8
 // with message terms 28 -> 26 us for 20,520 water atoms, 83 -> 75 for 65,856 and 845 -> 766 for 648,000;
 // K = 12 without 52 -> 48 us for 32,000 Cu atoms and 150 -> 137 for 100,800.  K = 12 with message
-// terms spills (64 -> 82 us for 32,000), and launches of few rows do not fill the chip.
+// terms spills (64 -> 82 us for 32,000), and launches of few rows do not fill the chip.  K = 8 without
+// message terms takes 114 registers, and so four waves, whichever it is held to.
 constexpr int centre_waves(int K, int LPR, bool CBAR) { return (K <= 8 || !CBAR) && LPR == 16 ? 4 : 3; }
 
 template <int L, int K, typename R, bool CBAR, int LPR, bool STREAM>
@@ -602,8 +604,9 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? centre_waves(K, LPR, CBAR) : 
 // F_k -= sum g and, with CBAR, cbar_k[m] = sum of the terms.  The reverse of an in-cutoff
 // entry is in cutoff (its displacement is the exact negation), so its compacted slot is set.
 // MAKE (the step's first gather) finds that slot through fslot, rev and cpos and stores it in
-// rslot, and sets the ghosts' F (nothing has written it yet); the later gathers read rslot.  With CBAR 4 lanes share an edge record (one group
-// of 4 values each, 8 edges per pass of the half-wave); without it a lane takes an edge.
+// rslot, and sets the ghosts' F (nothing has written it yet); the later gathers read rslot.  With
+// CBAR 4 lanes share an edge record (one group of 4 values each, 8 edges per pass of the half-wave);
+// without it a lane takes an edge.
 template <int K, typename R, bool CBAR, bool MAKE>
 __global__ __launch_bounds__(256) void k_adj_gather(EdgeArgs a, CutList cl, const R *__restrict__ rec,
                                                     R *__restrict__ F, R *__restrict__ cbar) {
@@ -623,7 +626,9 @@ __global__ __launch_bounds__(256) void k_adj_gather(EdgeArgs a, CutList cl, cons
     // the row's end are clamped to its last edge and their records are not added.  The reverse slots
     // of those edges are found with a lane per edge and handed out by permutes: with the edge's 4
     // lanes each loading it, the address unit was busy half the time (100,800 Cu atoms, first gather
-    // 235 us, 221 so; U = 4, 8, 12: 239, 226, 221).
+    // 235 us, 221 so; U = 4, 8, 12: 239, 226, 221).  Rows of fewer edges than a batch (water's 52 or so)
+    // load their last edge again, from the same lines, and do not tell U = 8 from 12: three gathers of
+    // 20,520 atoms 69.6 / 68.5 us, 65,772 214.6 / 215.1, 648,000 1,706 / 1,710.
     constexpr int U = CBAR ? 12 : 4, NI = U * EPP / 32;
     const int pc = part < NP ? 4 * part : 0;
     for (int b = 0; b < cnt; b += U * EPP) {

@@ -881,8 +881,9 @@ void Plan::backward(const double *d_g, double *d_forces, double *d_virial, hipSt
         mark(st, PH_ADJ_GATHER, 1);
         if (t > 0) {
             // message exchange: the ghosts' message adjoints go back to their owners here (the
-            // fused message NN adds them itself); node-feature exchange: the ghosts keep theirs (their message NN ran locally) and
-            // the adjoints of their orbital sums go back after the NN's VJP
+            // fused message NN adds them itself); node-feature exchange: the ghosts keep theirs
+            // (their message NN ran locally) and the adjoints of their orbital sums go back after
+            // the NN's VJP
             if (!nodefeat && !fused()) {
                 ghost_reduce(st, fp64, n, K, nl.copy_rng.ptr(), nl.copy_idx.ptr(), cbar.p);
                 mark(st, PH_GHOST);

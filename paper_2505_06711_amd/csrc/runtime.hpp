@@ -28,7 +28,8 @@ NNLayout nn_layout(int F, int H, int nh, int out);
 
 // Matrix-core operands of the hidden layers of every atomic NN: for NN q and hidden layer k,
 // the forward operand W_k and the backward operand W_k^T, packed (pack_operand) or for the
-// per-layer kernel as rows [dout][pad(din)] and [din][pad(dout)], in one operand type, with one scale per matrix (FP8: amax/448; otherwise 1).
+// per-layer kernel as rows [dout][pad(din)] and [din][pad(dout)], in one operand type, with one
+// scale per matrix (FP8: amax/448; otherwise 1).
 struct MfmaSet {
     DevBuf buf, scales;
     std::vector<size_t> off_fwd, off_bwd;   // bytes, index q * nh + k
